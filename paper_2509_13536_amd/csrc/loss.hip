@@ -1,28 +1,20 @@
 // Mapping loss of MemGS (Sec. II-E, Eq. (12)) for gfx950: colour L1, SSIM,
 // masked depth L1 and the isotropy term L_iso, value and gradient.
 //
-//   k_ssim_fwd    one 32x32 output tile of one colour channel per block: the
-//                 tile and a 5-pixel halo of both images staged in LDS; the five
-//                 window moments E[x], E[y], E[x^2], E[y^2], E[xy] by a
-//                 separable 11-tap pass (rows, then columns); per pixel SSIM and
-//                 its partial derivatives with respect to E[x], E[x^2] and E[xy]
-//                 (written for the second pass); block sums of SSIM and |x - y|.
-//                 Channel-0 blocks also form the depth residual and its gradient.
-//   k_ssim_bwd    the same tiling over the three derivative maps: their window
-//                 sums give d sum(SSIM) / d x, combined with the L1 subgradient.
-//   k_iso         one Gaussian per thread in fp64, so that the sign of each
+//   k_loss        one launch.  Blocks of SSIM tiles: value and gradient of the
+//                 SSIM and L1 terms of a strip of one colour channel, in one pass
+//                 over the images.  Blocks of the depth residual and its
+//                 gradient.  Blocks of L_iso, in fp64, so that the sign of each
 //                 scale's deviation from the mean scale is decided exactly.
-//   k_loss_views  one block per view (and one for L_iso): fixed-order fp64 sums
-//                 of the block partials; k_loss_total adds the views in order, so
-//                 the loss values are deterministic.
+//   k_loss_final  one block: fixed-order fp64 sums of the blocks' partial sums,
+//                 then the total in view order, so the values are deterministic.
 //
-// The SSIM work is a fixed 11-tap stencil, not a contraction: each pixel is
-// read once per pass and the moments stay in LDS.  Memory traffic per pixel and
-// channel: 8 bytes in and 12 out (first pass), 20 in and 4 out (second pass).
+// The colour terms move 8 bytes in and 4 out per pixel and channel.
 #include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "api_range.hpp"
@@ -31,324 +23,357 @@
 namespace mgs {
 namespace {
 
-constexpr int kLT = 32;             // output tile edge (pixels)
 constexpr int kLR = 5;              // window radius
 constexpr int kLW = 2 * kLR + 1;    // window taps
-constexpr int kLE = kLT + 2 * kLR;  // staged edge, 42
-constexpr int kLP = kLE + 1;        // padded LDS row of a staged map
-constexpr int kLH = kLT + 1;        // padded LDS row of a row-filtered map
-constexpr int kStageRows = 256 / kLE;            // staged rows per pass of the block (6)
-constexpr int kStageThreads = kStageRows * kLE;  // threads that stage (252)
-constexpr int kStageIt = (kLE + kStageRows - 1) / kStageRows;  // staged rows per thread (7)
 constexpr float kC1 = 1e-4f;        // (0.01)^2
 constexpr float kC2 = 9e-4f;        // (0.03)^2
 
 struct LossView {
-    int32_t W, H, TXn, pad;
-    int64_t tile_base;  // first tile of the view (tiles of one channel)
-    int64_t pix_base;   // first pixel in the packed one-channel layout
-    float inv_n3;       // 1 / (3 W H)
-    float inv_n1;       // 1 / (W H)
+    int32_t W, H;
+    int32_t strips, pad;  // strips of kSC columns
+    int64_t tile_base;    // first SSIM tile of the view (strips of one channel, cut into segments of rows)
+    int64_t pix_base;     // first pixel in the packed one-channel layout
+    int64_t depth_base;   // first block of k_loss_depth
+    float inv_n3;         // 1 / (3 W H)
+    float inv_n1;         // 1 / (W H)
+};
+
+// A call of at most kArgViews views carries its view table in the kernel
+// arguments; a larger one copies it to the workspace.
+constexpr int kArgViews = 16;
+struct ViewTable {
+    const LossView *table;  // null: the views are in own
+    LossView own[kArgViews];
+    int32_t n;
+    __device__ __forceinline__ const LossView &operator[](int v) const { return table ? table[v] : own[v]; }
 };
 
 struct SsimArgs {
-    const LossView *views;
-    int n_views;
+    ViewTable views;
     int64_t n_tiles;  // per channel
-    int64_t P;        // pixels of all views
-    const float *rgb, *gt, *depth, *gtd;
-    float *maps;      // three planes of 3P floats, packed like rgb
-    float *partial;   // [3][n_tiles][4]: SSIM sum, |x - y| sum, depth sum
-    float *d_rgb, *d_depth;
-    float lam, w_depth;
+    int nch;          // column chunks of a tile
+    const float *rgb, *gt;
+    float *partial;   // [3][n_tiles][2]: SSIM sum, |x - y| sum
+    float *d_rgb;
+    float lam;
     float w[kLW];     // normalised window weights
 };
 
-__device__ __forceinline__ int view_of_tile(const LossView *views, int V, int64_t t) {
-    int lo = 0, hi = V - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (views[mid].tile_base <= t) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 __device__ __forceinline__ float sgnf(float d) { return d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f); }
 
-// block sums of three values (256 threads); thread 0 gets the result
-__device__ __forceinline__ void block_sum3(float &a, float &b, float &c, float (*red)[4]) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
-    if (lane_id() == 0) {
-        red[0][threadIdx.x >> 6] = a;
-        red[1][threadIdx.x >> 6] = b;
-        red[2][threadIdx.x >> 6] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        a = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        b = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-        c = red[2][0] + red[2][1] + red[2][2] + red[2][3];
+// ---------------------------------------------------------------- colour: SSIM and L1
+// A block of four waves takes a strip of 54 output columns of one channel and
+// marches down its rows in chunks of 8.  The window is needed twice: over the
+// moments E[x], E[y], E[x^2 + y^2], E[xy] (the variances enter only as their
+// sum) and over the three derivative maps.  Both filters are carried along the
+// march, so the maps never leave the chip: memory sees x and y once (their halo
+// again through the caches) and the gradient.
+//
+// The two windows are 154 FMAs per pixel and channel, 63 us on 8 x 1200 x 680 at the
+// rate the vector units reach (2.6 cycles an FMA on a SIMD with vector operands
+// alone, 4.3 with a scalar one: the weights are kept in vector registers), and the
+// halo, the formula and the transposes about as much again.  x, y and the gradient
+// are 235 MB there, 50 us.  It takes 175 us, where two kernels with the maps in
+// memory between them took 348.  One wave for all signals of a strip carries 84
+// sums a lane and leaves two waves to a SIMD, which wait for each other's
+// memory: 174 us without the depth residual, and slower in a call of one view,
+// whose time is that of a chunk.  A wave for each signal carries 24.
+//
+//   A  wave w: signal w of the chunk's 8 rows (lanes = 8 rows x 8 bands of 8 map
+//      columns, 18 input columns a lane), filtered along x; transposed through
+//      LDS (lanes = the 64 map columns); along y, four rows at a time, the sums
+//      of the 12 rows in progress kept in registers
+//   B  wave t: SSIM and its derivatives of two of the eight complete map rows
+//   C  wave k < 3: map k along y; transposed (lanes = 8 rows x 8 bands of 7
+//      output columns); along x
+//      then, a wave two rows, the gradient
+//
+// A map row completes three quads of rows after its first input, an output row
+// another three: chunk j completes map rows 8 j - 12 .. - 5 and output rows
+// 8 j - 24 .. - 17 of the tile, which has 8 nch - 24 output rows.
+constexpr int kSC = 54;               // output columns of a strip
+constexpr int kWarm = 24;             // rows of warm-up of a tile
+constexpr int kIn = 8 + 2 * kLR;      // inputs of a band of 8 outputs along x
+constexpr int kInC = 64 + 2 * kLR;    // input columns of a strip
+constexpr int kStage = (8 * kInC + 255) / 256;  // staged values of a thread and image
+static_assert(kSC + 2 * kLR == 64, "the lane layouts");
+// LDS of one signal, in the row layout (row r at row_at(r)) or the column layout
+// (column c at 12 c): the 16-byte reads of a band's row, and those of a
+// column's rows, then meet no bank twice.
+constexpr int kSig = 768, kRows = 648;
+__device__ __forceinline__ constexpr int row_at(int r) { return 80 * r + 4 * (r >> 2); }
+static_assert(kInC <= 80 && row_at(7) + 80 <= kRows && 12 * 63 + 8 <= kSig, "LDS of a signal");
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
     }
 }
 
-// Tile origin and channel base of this block.  Workgroups are dealt to the
-// eight XCDs round robin (block b on XCD b % 8); each XCD gets a contiguous run
-// of tiles, so the halo a tile shares with its neighbours is read through the
-// same L2.  The grid has 8 ceil(n / 8) blocks; those past the last tile exit.
-struct TileAt {
-    LossView V;
-    int64_t tile;
-    bool valid;
-    int ox, oy;
-    int64_t cbase;  // offset of this view's channel plane in the packed colour layout
-};
-__device__ __forceinline__ TileAt tile_at(const SsimArgs &a) {
-    TileAt t;
-    const int64_t per = (a.n_tiles + 7) / 8;
-    const int64_t tile = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    t.tile = tile;
-    t.valid = tile < a.n_tiles;
-    if (!t.valid) return t;
-    t.V = a.views[view_of_tile(a.views, a.n_views, tile)];
-    const int lt = (int)(tile - t.V.tile_base), ty = lt / t.V.TXn, tx = lt - ty * t.V.TXn;
-    t.ox = tx * kLT;
-    t.oy = ty * kLT;
-    t.cbase = 3 * t.V.pix_base + (int64_t)blockIdx.y * t.V.W * t.V.H;
-    return t;
+// LDS written by lanes of this wave, then read by other lanes of it
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(256) void k_ssim_fwd(SsimArgs a) {
-    // the staged images and the row-filtered moments share the LDS: the rows
-    // pass keeps its results in registers until every thread has read the images
-    __shared__ float lds[5 * kLE * kLH];
-    __shared__ float red[3][4];
-    float(*sx)[kLP] = reinterpret_cast<float(*)[kLP]>(lds);
-    float(*sy)[kLP] = reinterpret_cast<float(*)[kLP]>(lds + kLE * kLP);
-    float(*hm)[kLE][kLH] = reinterpret_cast<float(*)[kLE][kLH]>(lds);
-    static_assert(2 * kLE * kLP <= 5 * kLE * kLH, "staged images fit in the moments' space");
-    const TileAt T = tile_at(a);
-    if (!T.valid) return;  // the whole block
-    const LossView &V = T.V;
-    const int c = blockIdx.y, tid = threadIdx.x;
-    const float *X = a.rgb + T.cbase, *Y = a.gt + T.cbase;
-    float sL = 0.0f;  // |x - y| over this tile's pixels
-    {
-        // staging: thread t owns staged column t % 42 of rows t / 42 + 6 k; every
-        // load is issued before the first wait
-        const int q = tid % kLE, r0 = tid / kLE;
-        const int gx = T.ox - kLR + q;
-        const bool stager = tid < kStageThreads;
-        const bool colok = stager && gx >= 0 && gx < V.W;
-        const bool inner_col = q >= kLR && q < kLR + kLT;
-        float xv[kStageIt], yv[kStageIt];
+__device__ __forceinline__ int uniform_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// acc[m] += w[K - m] v for a group's four outputs
+template <int K>
+__device__ __forceinline__ void mac4(const float *w, float v, f4 &acc) {
 #pragma unroll
-        for (int k = 0; k < kStageIt; ++k) {
-            const int r = r0 + k * kStageRows, gy = T.oy - kLR + r;
-            xv[k] = yv[k] = 0.0f;
-            if (colok && r < kLE && gy >= 0 && gy < V.H) {
-                const int64_t o = (int64_t)gy * V.W + gx;
-                xv[k] = X[o];
-                yv[k] = Y[o];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kStageIt; ++k) {
-            const int r = r0 + k * kStageRows;
-            if (!stager || r >= kLE) continue;
-            sx[r][q] = xv[k];
-            sy[r][q] = yv[k];
-            if (inner_col && r >= kLR && r < kLR + kLT) sL += fabsf(xv[k] - yv[k]);
-        }
-    }
-    __syncthreads();
-    // rows: the five moments filtered along x for every staged row
-    constexpr int kRowIt = (kLE * kLT + 255) / 256;
-    float hv[kRowIt][5];
-#pragma unroll
-    for (int it = 0; it < kRowIt; ++it) {
-        const int i = tid + 256 * it;
-        const int r = i >> 5, q = i & 31;
-        float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
-        if (i < kLE * kLT) {
-#pragma unroll
-            for (int o = 0; o < kLW; ++o) {
-                const float xv = sx[r][q + o], yv = sy[r][q + o], w = a.w[o];
-                const float wx = w * xv, wy = w * yv;
-                m0 += wx;
-                m1 += wy;
-                m2 = __builtin_fmaf(wx, xv, m2);
-                m3 = __builtin_fmaf(wy, yv, m3);
-                m4 = __builtin_fmaf(wx, yv, m4);
-            }
-        }
-        hv[it][0] = m0;
-        hv[it][1] = m1;
-        hv[it][2] = m2;
-        hv[it][3] = m3;
-        hv[it][4] = m4;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < kRowIt; ++it) {
-        const int i = tid + 256 * it;
-        if (i < kLE * kLT)
-#pragma unroll
-            for (int k = 0; k < 5; ++k) hm[k][i >> 5][i & 31] = hv[it][k];
-    }
-    __syncthreads();
-    // columns: thread (q, g) finishes rows 4g .. 4g+3 of column q
-    const int q = tid & 31, g4 = (tid >> 5) * 4;
-    float acc[4][5];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) acc[j][k] = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kLW + 3; ++o) {
-        float h[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) h[k] = hm[k][g4 + o][q];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int tap = o - j;
-            if (tap < 0 || tap >= kLW) continue;
-#pragma unroll
-            for (int k = 0; k < 5; ++k) acc[j][k] = __builtin_fmaf(a.w[tap], h[k], acc[j][k]);
-        }
-    }
-    float sS = 0.0f, sD = 0.0f;
-    const int64_t P3 = 3 * a.P;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = g4 + j, gx = T.ox + q, gy = T.oy + r;
-        if (gx >= V.W || gy >= V.H) continue;
-        const float mx = acc[j][0], my = acc[j][1];
-        const float vx = acc[j][2] - mx * mx, vy = acc[j][3] - my * my, cxy = acc[j][4] - mx * my;
-        const float A = 2.0f * mx * my + kC1, B = 2.0f * cxy + kC2;
-        const float C = mx * mx + my * my + kC1, D = vx + vy + kC2;
-        const float iA = __builtin_amdgcn_rcpf(A), iB = __builtin_amdgcn_rcpf(B);
-        const float iC = __builtin_amdgcn_rcpf(C), iD = __builtin_amdgcn_rcpf(D);
-        const float S = A * B * iC * iD;
-        const int64_t o = (int64_t)gy * V.W + gx;
-        float *M = a.maps + T.cbase + o;
-        M[0] = 2.0f * S * (my * iA - mx * iC + mx * iD - my * iB);
-        M[P3] = -S * iD;
-        M[2 * P3] = 2.0f * S * iB;
-        sS += S;
-        if (c == 0 && a.depth) {
-            const int64_t pix = V.pix_base + o;
-            const float gd = a.gtd[pix];
-            const float dd = gd > 0.0f ? a.depth[pix] - gd : 0.0f;
-            sD += fabsf(dd);
-            a.d_depth[pix] = a.w_depth * V.inv_n1 * sgnf(dd);
-        }
-    }
-    block_sum3(sS, sL, sD, red);
-    if (tid == 0) {
-        float *p = a.partial + ((int64_t)c * a.n_tiles + T.tile) * 4;
-        p[0] = sS;
-        p[1] = sL;
-        p[2] = sD;
-        p[3] = 0.0f;
-    }
+    for (int m = 0; m < 4; ++m)
+        if (K - m >= 0 && K - m < kLW) acc[m] = __builtin_fmaf(w[K - m], v, acc[m]);
 }
 
-__global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs a) {
-    // staged maps and their row-filtered sums share the LDS (as in k_ssim_fwd)
-    __shared__ float lds[3 * kLE * kLP];
-    float(*sm)[kLE][kLP] = reinterpret_cast<float(*)[kLE][kLP]>(lds);
-    float(*hm)[kLE][kLH] = reinterpret_cast<float(*)[kLE][kLH]>(lds);
-    const TileAt T = tile_at(a);
-    if (!T.valid) return;  // the whole block
-    const LossView &V = T.V;
-    const int tid = threadIdx.x;
-    const int64_t P3 = 3 * a.P;
-    const float *M = a.maps + T.cbase;
-    {
-        const int q = tid % kLE, r0 = tid / kLE;
-        const int gx = T.ox - kLR + q;
-        const bool stager = tid < kStageThreads;
-        const bool colok = stager && gx >= 0 && gx < V.W;
-        float mv[kStageIt][3];
+// Filtering along y: four new rows into the three groups of four outputs in
+// progress (oldest first) and a new one; the oldest completes.
+__device__ __forceinline__ f4 next_quad(const float *w, f4 in, f4 (&g)[3]) {
+    f4 n = {0.0f, 0.0f, 0.0f, 0.0f};
+    mac4<12>(w, in[0], g[0]);
+    mac4<13>(w, in[1], g[0]);
+    static_for<4>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        mac4<8 + c>(w, in[c], g[1]);
+        mac4<4 + c>(w, in[c], g[2]);
+        mac4<c>(w, in[c], n);
+    });
+    const f4 done = g[0];
+    g[0] = g[1];
+    g[1] = g[2];
+    g[2] = n;
+    return done;
+}
+
+__device__ __forceinline__ float plane_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+
+// A band's eight outputs along x from its row at p; get(k): inputs 4 k .. 4 k + 3.
+// One quad of inputs at a time, which keeps the registers few.
+template <class F>
+__device__ __forceinline__ void filter_band(const float *w, F &&get, f4 (&v)[2]) {
+    v[0] = v[1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    static_for<5>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        const f4 x = get(kc);
 #pragma unroll
-        for (int k = 0; k < kStageIt; ++k) {
-            const int r = r0 + k * kStageRows, gy = T.oy - kLR + r;
-            mv[k][0] = mv[k][1] = mv[k][2] = 0.0f;
-            if (colok && r < kLE && gy >= 0 && gy < V.H) {
-                const int64_t o = (int64_t)gy * V.W + gx;
-                mv[k][0] = M[o];
-                mv[k][1] = M[P3 + o];
-                mv[k][2] = M[2 * P3 + o];
+        for (int i = 0; i < (k < 4 ? 4 : 2); ++i)
+#pragma unroll
+            for (int o = 0; o < 8; ++o)
+                if (4 * k + i - o >= 0 && 4 * k + i - o < kLW)
+                    v[o >> 2][o & 3] = __builtin_fmaf(w[4 * k + i - o], x[i], v[o >> 2][o & 3]);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// One tile of one channel: item = channel * n_tiles + tile.
+__device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
+    __shared__ __attribute__((aligned(16))) float mom[4][kSig], map[3][kSig], img[2][kRows];
+    __shared__ float red[2][4];
+    const int c = (int)(item / a.n_tiles);
+    const int64_t tile = item - c * a.n_tiles;
+    int lo = 0, hi = a.views.n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (a.views[mid].tile_base <= tile) lo = mid; else hi = mid - 1;
+    }
+    const LossView &V = a.views[lo];
+    // scalars (the view's address may be in either memory, so the compiler
+    // would take what it loads for a lane's own)
+    const int W = uniform_i(V.W), H = uniform_i(V.H), strips = uniform_i(V.strips);
+    const int64_t pix_base = (int64_t)(uint32_t)uniform_i((int)V.pix_base) | ((int64_t)uniform_i((int)(V.pix_base >> 32)) << 32);
+    const float inv_n3 = V.inv_n3;
+    const int lt = uniform_i((int)(tile - V.tile_base)), sg = lt / strips;
+    const int c0 = (lt - sg * strips) * kSC, r0 = sg * (8 * a.nch - kWarm);
+    const int rend = min(r0 + 8 * a.nch - kWarm, H);  // output rows [r0, rend)
+    const int lane = lane_id(), w = uniform_i((int)threadIdx.x >> 6);
+    const int band = lane >> 3, row = lane & 7;
+    const int64_t plane = (int64_t)W * H, cbase = 3 * pix_base + c * plane;
+    // rows and columns outside the image read as zero: their offset is one past
+    // the plane
+    const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.rgb + cbase), (short)0, (int)(4 * plane), 0x00027000);
+    const auto ry = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.gt + cbase), (short)0, (int)(4 * plane), 0x00027000);
+    constexpr uint32_t kOutside = 0x80000000u;
+    const uint32_t pitch = 4u * (uint32_t)W;
+    const int map_col = c0 - kLR + lane;              // this lane's map column in the column layout
+    const bool col_in = map_col >= 0 && map_col < W;
+    const bool col_own = col_in && lane >= kLR && lane < kLR + kSC;
+    const int ox = c0 + lane;                         // and its output column
+    const bool out_own = lane < kSC && ox < W;
+    const int at_col = 12 * lane;                     // its place in the column layout
+    const int at_band = row_at(row) + 8 * band;       // this lane's band of 8 in the row layout
+    const float kl1 = (1.0f - a.lam) * inv_n3, ks = a.lam * inv_n3;
+    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f4 g1[3] = {zero, zero, zero}, g2[3] = {zero, zero, zero};
+    // the weights in vector registers: an FMA with a scalar operand issues at
+    // about half the rate
+    float wv[kLW];
+#pragma unroll
+    for (int o = 0; o <= kLR; ++o) {
+        float t = a.w[o];
+        asm volatile("" : "+v"(t));
+        wv[o] = wv[kLW - 1 - o] = t;
+    }
+    float sS = 0.0f, sL = 0.0f;
+    float xo[2], yo[2];  // x and y of this wave's two output rows
+    // staging of a chunk's 8 x 74 values of both images: loaded a chunk ahead
+    float xs[kStage], ys[kStage];
+    uint32_t soff[kStage];
+    int slds[kStage];
+#pragma unroll
+    for (int k = 0; k < kStage; ++k) {
+        const int i = (int)threadIdx.x + 256 * k, r = i / kInC, q = i - r * kInC, gx = c0 - 2 * kLR + q;
+        const bool in = r < 8 && gx >= 0 && gx < W;
+        soff[k] = in ? (uint32_t)(r0 - 2 * kLR + r) * pitch + 4u * (uint32_t)gx : kOutside;
+        slds[k] = r < 8 ? row_at(r) + q : kInC;  // a spare place
+    }
+    auto stage_load = [&]() {
+#pragma unroll
+        for (int k = 0; k < kStage; ++k) {
+            xs[k] = plane_load(rx, soff[k]);
+            ys[k] = plane_load(ry, soff[k]);
+            soff[k] += 8 * pitch;
+        }
+    };
+    auto stage_store = [&]() {
+#pragma unroll
+        for (int k = 0; k < kStage; ++k) {
+            img[0][slds[k]] = xs[k];
+            img[1][slds[k]] = ys[k];
+        }
+    };
+    stage_load();
+    stage_store();
+    stage_load();
+    __syncthreads();
+    float *const my = mom[w];
+    // the gradient of the 8 rows from gy0 on, from the maps' sums in LDS
+    auto finish = [&](int gy0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int r = 2 * w + u, oy = gy0 + r;  // uniform
+            if (oy >= rend) break;
+            if (out_own) {
+                const float o0 = map[0][row_at(r) + lane], o1 = map[1][row_at(r) + lane], o2 = map[2][row_at(r) + lane];
+                const float d = xo[u] - yo[u];
+                const float gs = __builtin_fmaf(yo[u], o2, __builtin_fmaf(2.0f * xo[u], o1, o0));
+                a.d_rgb[cbase + (int64_t)oy * W + ox] = __builtin_fmaf(-ks, gs, kl1 * sgnf(d));
+                sL += fabsf(d);
             }
         }
+    };
+    for (int j = 0; j < a.nch; ++j) {
+        // A
+        {
+            if (j > 3) finish(r0 + 8 * (j - 1) - kWarm);
+            f4 v[2];
+            const float *const x = img[0] + at_band, *const y = img[1] + at_band;
+            auto quad = [](const float *p, auto kc) { return *reinterpret_cast<const f4 *>(p + 4 * decltype(kc)::value); };
+            if (w < 2) {
+                const float *const p = w == 0 ? x : y;
+                filter_band(wv, [&](auto kc) { return quad(p, kc); }, v);
+            } else if (w == 2) {
+                filter_band(wv, [&](auto kc) {
+                    const f4 p = quad(x, kc), q = quad(y, kc);
+                    f4 e;
 #pragma unroll
-        for (int k = 0; k < kStageIt; ++k) {
-            const int r = r0 + k * kStageRows;
-            if (!stager || r >= kLE) continue;
-            sm[0][r][q] = mv[k][0];
-            sm[1][r][q] = mv[k][1];
-            sm[2][r][q] = mv[k][2];
+                    for (int i = 0; i < 4; ++i) e[i] = __builtin_fmaf(p[i], p[i], q[i] * q[i]);
+                    return e;
+                }, v);
+            } else {
+                filter_band(wv, [&](auto kc) { return quad(x, kc) * quad(y, kc); }, v);
+            }
+            *reinterpret_cast<f4 *>(my + at_band) = v[0];
+            *reinterpret_cast<f4 *>(my + at_band + 4) = v[1];
+            wave_lds_sync();
+            f4 q0, q1;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                q0[r] = my[row_at(r) + lane];
+                q1[r] = my[row_at(r + 4) + lane];
+            }
+            wave_lds_sync();
+            const f4 d0 = next_quad(wv, q0, g1), d1 = next_quad(wv, q1, g1);
+            *reinterpret_cast<f4 *>(my + at_col) = d0;
+            *reinterpret_cast<f4 *>(my + at_col + 4) = d1;
         }
-    }
-    __syncthreads();
-    constexpr int kRowIt = (kLE * kLT + 255) / 256;
-    float hv[kRowIt][3];
+        __syncthreads();
+        // B
+        stage_store();
+        stage_load();
+        {
+            const f2 mx2 = *reinterpret_cast<const f2 *>(mom[0] + at_col + 2 * w), my2 = *reinterpret_cast<const f2 *>(mom[1] + at_col + 2 * w);
+            const f2 e2 = *reinterpret_cast<const f2 *>(mom[2] + at_col + 2 * w), p2 = *reinterpret_cast<const f2 *>(mom[3] + at_col + 2 * w);
+            f2 M[3];
 #pragma unroll
-    for (int it = 0; it < kRowIt; ++it) {
-        const int i = tid + 256 * it;
-        const int r = i >> 5, q = i & 31;
-        float h0 = 0.f, h1 = 0.f, h2 = 0.f;
-        if (i < kLE * kLT) {
+            for (int u = 0; u < 2; ++u) {
+                const int gy = r0 - kLR + 8 * j - 12 + 2 * w + u;  // uniform
+                const bool in = col_in && gy >= 0 && gy < H;
+                const float mx = mx2[u], my = my2[u], e = e2[u], p = p2[u];
+                const float mxy = mx * my, q = __builtin_fmaf(mx, mx, my * my);
+                const float A = __builtin_fmaf(2.0f, mxy, kC1), B = __builtin_fmaf(2.0f, p - mxy, kC2);
+                const float iC = __builtin_amdgcn_rcpf(q + kC1), iD = __builtin_amdgcn_rcpf((e - q) + kC2);
+                const float i2 = iC * iD;
+                const float S = A * B * i2;
+                const float d0 = 2.0f * __builtin_fmaf(my * (B - A), i2, mx * S * (iD - iC));
+                M[0][u] = in ? d0 : 0.0f;
+                M[1][u] = in ? -S * iD : 0.0f;
+                M[2][u] = in ? 2.0f * A * i2 : 0.0f;
+                if (gy >= r0 && gy < rend) sS += col_own ? S : 0.0f;
+            }
 #pragma unroll
-            for (int o = 0; o < kLW; ++o) {
-                const float w = a.w[o];
-                h0 = __builtin_fmaf(w, sm[0][r][q + o], h0);
-                h1 = __builtin_fmaf(w, sm[1][r][q + o], h1);
-                h2 = __builtin_fmaf(w, sm[2][r][q + o], h2);
+            for (int k = 0; k < 3; ++k) *reinterpret_cast<f2 *>(map[k] + at_col + 2 * w) = M[k];
+        }
+        __syncthreads();
+        // C
+        if (j >= 3) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int oy = r0 + 8 * j - kWarm + 2 * w + u;
+                const uint32_t off = out_own && oy < H ? (uint32_t)oy * pitch + 4u * (uint32_t)ox : kOutside;
+                xo[u] = plane_load(rx, off);
+                yo[u] = plane_load(ry, off);
             }
         }
-        hv[it][0] = h0;
-        hv[it][1] = h1;
-        hv[it][2] = h2;
-    }
-    __syncthreads();
+        if (w < 3) {
+            float *const mp = map[w];
+            const f4 q0 = *reinterpret_cast<const f4 *>(mp + at_col), q1 = *reinterpret_cast<const f4 *>(mp + at_col + 4);
+            wave_lds_sync();
+            const f4 d0 = next_quad(wv, q0, g2), d1 = next_quad(wv, q1, g2);
+            if (j >= 3) {
 #pragma unroll
-    for (int it = 0; it < kRowIt; ++it) {
-        const int i = tid + 256 * it;
-        if (i < kLE * kLT)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) hm[k][i >> 5][i & 31] = hv[it][k];
-    }
-    __syncthreads();
-    const int q = tid & 31, g4 = (tid >> 5) * 4;
-    float acc[4][3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j][0] = acc[j][1] = acc[j][2] = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kLW + 3; ++o) {
-        const float h0 = hm[0][g4 + o][q], h1 = hm[1][g4 + o][q], h2 = hm[2][g4 + o][q];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int tap = o - j;
-            if (tap < 0 || tap >= kLW) continue;
-            acc[j][0] = __builtin_fmaf(a.w[tap], h0, acc[j][0]);
-            acc[j][1] = __builtin_fmaf(a.w[tap], h1, acc[j][1]);
-            acc[j][2] = __builtin_fmaf(a.w[tap], h2, acc[j][2]);
+                for (int r = 0; r < 4; ++r) {
+                    mp[row_at(r) + lane] = d0[r];
+                    mp[row_at(r + 4) + lane] = d1[r];
+                }
+                wave_lds_sync();
+                f4 v[2];
+                filter_band(wv, [&](auto kc) { return *reinterpret_cast<const f4 *>(mp + at_band + 4 * decltype(kc)::value); }, v);
+                wave_lds_sync();
+                *reinterpret_cast<f4 *>(mp + at_band) = v[0];
+                *reinterpret_cast<f4 *>(mp + at_band + 4) = v[1];
+            }
         }
+        __syncthreads();
     }
-    const float kl1 = (1.0f - a.lam) * V.inv_n3, ks = a.lam * V.inv_n3;
-    const float *X = a.rgb + T.cbase, *Y = a.gt + T.cbase;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int gx = T.ox + q, gy = T.oy + g4 + j;
-        if (gx >= V.W || gy >= V.H) continue;
-        const int64_t o = (int64_t)gy * V.W + gx;
-        const float x = X[o], y = Y[o];
-        const float gs = acc[j][0] + 2.0f * x * acc[j][1] + y * acc[j][2];
-        a.d_rgb[T.cbase + o] = kl1 * sgnf(x - y) - ks * gs;
+    finish(r0 + 8 * (a.nch - 1) - kWarm);
+    sS = wave_sum(sS);
+    sL = wave_sum(sL);
+    if (lane == 0) {
+        red[0][w] = sS;
+        red[1][w] = sL;
     }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *reinterpret_cast<float2 *>(a.partial + 2 * item) =
+            make_float2((red[0][0] + red[0][1]) + (red[0][2] + red[0][3]), (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
 }
 
 __device__ __forceinline__ double sgnd(double d) { return d > 0.0 ? 1.0 : (d < 0.0 ? -1.0 : 0.0); }
@@ -358,100 +383,177 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
     return x;
 }
 
-// L_iso per Gaussian: deviations of the three scales from their mean
-__global__ __launch_bounds__(256) void k_iso(const float *scales, int64_t n, float w_iso, float *d_scales,
-                                             double *partial) {
+// ---------------------------------------------------------------- depth and L_iso
+constexpr int kDepthPix = 8192;  // pixels of one view that a block takes
+constexpr int kIsoGauss = 1024;  // Gaussians that a block of L_iso takes
+
+struct RestArgs {
+    int64_t n_depth;  // blocks of the depth residual
+    const float *depth, *gtd;
+    float *d_depth, *depth_partial;
+    float w_depth;
+    const float *scales;
+    int64_t n;
+    float w_iso;
+    float *d_scales;
+    double *iso_partial;
+};
+
+__device__ __forceinline__ void depth_block(const RestArgs &a, const ViewTable &views, int64_t b) {
+    __shared__ float red[4];
+    int lo = 0, hi = views.n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (views[mid].depth_base <= b) lo = mid; else hi = mid - 1;
+    }
+    const LossView &V = views[lo];
+    const int64_t n = (int64_t)V.W * V.H, base = (b - V.depth_base) * kDepthPix;
+    const float *D = a.depth + V.pix_base, *G = a.gtd + V.pix_base;
+    const float k = a.w_depth * V.inv_n1;
+    float sum = 0.0f;
+    for (int64_t i0 = base + threadIdx.x; i0 < base + kDepthPix; i0 += 256 * 8) {
+        float d[8], g[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int64_t i = i0 + 256 * r;
+            d[r] = i < n ? D[i] : 0.0f;
+            g[r] = i < n ? G[i] : 0.0f;
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const float e = g[r] > 0.0f ? d[r] - g[r] : 0.0f;
+            sum += fabsf(e);
+            if (i0 + 256 * r < n) a.d_depth[V.pix_base + i0 + 256 * r] = k * sgnf(e);
+        }
+    }
+    sum = wave_sum(sum);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) a.depth_partial[b] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// deviations of the Gaussians' three scales from their mean
+__device__ __forceinline__ void iso_block(const RestArgs &a, int64_t b) {
     __shared__ double red[4];
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double acc = 0.0;
-    if (g < n) {
-        const double s0 = scales[3 * g], s1 = scales[3 * g + 1], s2 = scales[3 * g + 2];
+    const double k = (double)a.w_iso / (3.0 * (double)a.n);
+    for (int64_t g = b * kIsoGauss + threadIdx.x; g < std::min<int64_t>(a.n, (b + 1) * kIsoGauss); g += 256) {
+        const double s0 = a.scales[3 * g], s1 = a.scales[3 * g + 1], s2 = a.scales[3 * g + 2];
         const double m = (s0 + s1 + s2) / 3.0;
         const double e0 = s0 - m, e1 = s1 - m, e2 = s2 - m;
-        acc = fabs(e0) + fabs(e1) + fabs(e2);
+        acc += fabs(e0) + fabs(e1) + fabs(e2);
         const double g0 = sgnd(e0), g1 = sgnd(e1), g2 = sgnd(e2);
         const double mg = (g0 + g1 + g2) / 3.0;
-        const double k = (double)w_iso / (3.0 * (double)n);
-        d_scales[3 * g] = (float)(k * (g0 - mg));
-        d_scales[3 * g + 1] = (float)(k * (g1 - mg));
-        d_scales[3 * g + 2] = (float)(k * (g2 - mg));
+        a.d_scales[3 * g] = (float)(k * (g0 - mg));
+        a.d_scales[3 * g + 1] = (float)(k * (g1 - mg));
+        a.d_scales[3 * g + 2] = (float)(k * (g2 - mg));
     }
     acc = wave_sum_f64(acc);
     if (lane_id() == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x == 0) a.iso_partial[b] = red[0] + red[1] + red[2] + red[3];
 }
 
+// The whole loss but its sums, in one launch: the SSIM tiles, which issue is the
+// bound of, then blocks of the depth residual and of L_iso, which memory is, in
+// the room that the last tiles leave.  Workgroups are dealt to the eight XCDs
+// round robin (block b on XCD b % 8); each XCD gets a contiguous run of tiles, so
+// the halo a tile shares with its neighbours is read through the same L2.  The
+// tiles have 8 ceil(n / 8) blocks; those past the last tile exit.
+__global__ __launch_bounds__(256, 5) void k_loss(SsimArgs a, RestArgs r) {
+    const int64_t n = 3 * a.n_tiles, per = (n + 7) / 8, b = blockIdx.x;
+    if (b < 8 * per) {
+        const int64_t item = (b & 7) * per + (b >> 3);
+        if (item < n) ssim_tile(a, item);
+    } else if (b - 8 * per < r.n_depth) {
+        depth_block(r, a.views, b - 8 * per);
+    } else {
+        iso_block(r, b - 8 * per - r.n_depth);
+    }
+}
+
+// ---------------------------------------------------------------- values
 struct FinalArgs {
-    const LossView *views;
-    int n_views;
-    int64_t n_tiles;
-    const float *partial;
+    ViewTable views;
+    int64_t n_tiles, n_depth;
+    const float *partial, *depth_partial;
     const double *iso_partial;
     int64_t n_iso_blocks;
     int64_t n_gauss;
     float lam, w_depth, w_iso;
     int has_depth;
-    double *terms;  // [n_views + 1]: L_view of each view, then L_iso
+    double *terms;  // [n_views]: L_view of each view
     float *loss;    // [4 n_views + 2]
 };
 
-__device__ __forceinline__ double block_sum_f64(double x, double *red) {
-    x = wave_sum_f64(x);
-    if (lane_id() == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    const double r = red[0] + red[1] + red[2] + red[3];
-    __syncthreads();
-    return r;
-}
-
-// block v < n_views: the terms of view v; block n_views: L_iso
-__global__ __launch_bounds__(256) void k_loss_views(FinalArgs a) {
-    __shared__ double red[4];
-    const int tid = threadIdx.x, v = blockIdx.x;
-    if (v == a.n_views) {
-        double si = 0.0;
-        for (int64_t b = tid; b < a.n_iso_blocks; b += 256) si += a.iso_partial[b];
-        si = block_sum_f64(si, red);
-        const double liso = a.n_gauss > 0 ? (double)a.w_iso * si / (3.0 * (double)a.n_gauss) : 0.0;
-        if (tid == 0) {
-            a.terms[v] = liso;
-            a.loss[4 * v] = (float)liso;
+// One block of 16 waves: a round takes up to 16 views, with 16 / views waves each;
+// then L_iso over the block and the total in view order.
+__global__ __launch_bounds__(1024) void k_loss_final(FinalArgs a) {
+    __shared__ double red[3][16];
+    const int lane = lane_id(), wave = threadIdx.x >> 6, nv = a.views.n;
+    const int at_once = nv < 16 ? nv : 16, share = 16 / at_once;
+    for (int v0 = 0; v0 < nv; v0 += at_once) {
+        const int v = v0 + wave / share;
+        double sS = 0.0, sL = 0.0, sD = 0.0;
+        if (wave < at_once * share && v < nv) {
+            const int64_t t0 = a.views[v].tile_base, t1 = v + 1 < nv ? a.views[v + 1].tile_base : a.n_tiles;
+            const int64_t b0 = a.views[v].depth_base, b1 = v + 1 < nv ? a.views[v + 1].depth_base : a.n_depth;
+            const int64_t first = (wave % share) * 64 + lane, step = share * 64;
+            for (int64_t t = t0 + first; t < t1; t += step) {
+                float2 p[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) p[c] = *reinterpret_cast<const float2 *>(a.partial + 2 * (c * a.n_tiles + t));
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    sS += p[c].x;
+                    sL += p[c].y;
+                }
+            }
+            if (a.has_depth)
+                for (int64_t b = b0 + first; b < b1; b += step) sD += a.depth_partial[b];
         }
-        return;
-    }
-    const LossView V = a.views[v];
-    const int64_t t1 = v + 1 < a.n_views ? a.views[v + 1].tile_base : a.n_tiles;
-    const int64_t nt = t1 - V.tile_base;
-    double sS = 0.0, sL = 0.0, sD = 0.0;
-    for (int c = 0; c < 3; ++c)
-        for (int64_t t = tid; t < nt; t += 256) {
-            const float4 p = *reinterpret_cast<const float4 *>(a.partial + ((int64_t)c * a.n_tiles + V.tile_base + t) * 4);
-            sS += p.x;
-            sL += p.y;
-            sD += p.z;
+        sS = wave_sum_f64(sS);
+        sL = wave_sum_f64(sL);
+        sD = wave_sum_f64(sD);
+        if (lane == 0) {
+            red[0][wave] = sS;
+            red[1][wave] = sL;
+            red[2][wave] = sD;
         }
-    sS = block_sum_f64(sS, red);
-    sL = block_sum_f64(sL, red);
-    sD = block_sum_f64(sD, red);
-    if (tid == 0) {
-        const double npx = (double)V.W * (double)V.H;
-        const double l1 = sL / (3.0 * npx), ssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
-        const double lv = (1.0 - a.lam) * l1 + a.lam * (1.0 - ssim) + (a.has_depth ? a.w_depth * ld : 0.0);
-        a.terms[v] = lv;
-        a.loss[4 * v] = (float)l1;
-        a.loss[4 * v + 1] = (float)ssim;
-        a.loss[4 * v + 2] = (float)ld;
-        a.loss[4 * v + 3] = (float)lv;
+        __syncthreads();
+        const int u = v0 + (int)threadIdx.x;
+        if ((int)threadIdx.x < at_once && u < nv) {
+            const double npx = (double)a.views[u].W * (double)a.views[u].H;
+            sS = sL = sD = 0.0;
+            for (int i = 0; i < share; ++i) {
+                sS += red[0][threadIdx.x * share + i];
+                sL += red[1][threadIdx.x * share + i];
+                sD += red[2][threadIdx.x * share + i];
+            }
+            const double l1 = sL / (3.0 * npx), ssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
+            const double lv = (1.0 - a.lam) * l1 + a.lam * (1.0 - ssim) + (a.has_depth ? a.w_depth * ld : 0.0);
+            a.terms[u] = lv;
+            a.loss[4 * u] = (float)l1;
+            a.loss[4 * u + 1] = (float)ssim;
+            a.loss[4 * u + 2] = (float)ld;
+            a.loss[4 * u + 3] = (float)lv;
+        }
+        __syncthreads();
     }
-}
-
-// the total, summed in view order
-__global__ void k_loss_total(const double *terms, int n_views, float *loss) {
+    double si = 0.0;
+    for (int64_t b = threadIdx.x; b < a.n_iso_blocks; b += 1024) si += a.iso_partial[b];
+    si = wave_sum_f64(si);
+    if (lane == 0) red[0][wave] = si;
+    __threadfence_block();  // the views' terms, read below by thread 0
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    double t = 0.0;
-    for (int v = 0; v <= n_views; ++v) t += terms[v];
-    loss[4 * n_views + 1] = (float)t;
+    double iso = 0.0, total = 0.0;
+    for (int w = 0; w < 16; ++w) iso += red[0][w];
+    iso = a.n_gauss > 0 ? (double)a.w_iso * iso / (3.0 * (double)a.n_gauss) : 0.0;
+    for (int v = 0; v < nv; ++v) total += a.terms[v];
+    total += iso;
+    a.loss[4 * nv] = (float)iso;
+    a.loss[4 * nv + 1] = (float)total;
 }
 
 }  // namespace
@@ -479,65 +581,96 @@ mgs_status loss_check(const int32_t *sizes, int32_t n_views, const float *rgb, c
     return MGS_OK;
 }
 
+// Row chunks of an SSIM tile.  A tile of nch chunks yields 8 nch - 24 rows (the
+// first 24 warm the two filters up), so tall tiles do less work, but a call must
+// also fill the chip and end evenly.  In units of one block's chunk on a CU that
+// holds several (0.75 us): a chunk takes a block alone three, and the last blocks
+// of a call two and a half beyond their CU's share.  Measured: 641 x 479, 24.5 us
+// at 5 chunks, 22.4 at 6, 24.9 at 7, 33 at 13; 8 x 1200 x 680, 234 us at 8, 214 at
+// 13, 190 at 18, 182 at 20, 185 at 32.
+int ssim_chunks(const int32_t *sizes, int32_t n_views) {
+    int best = 4;
+    double least = 0.0;
+    for (int nch = 4; nch <= 40; ++nch) {
+        int64_t blocks = 0;
+        for (int v = 0; v < n_views; ++v)
+            blocks += 3 * ceil_div(sizes[2 * v + 1], 8 * nch - kWarm) * ceil_div(sizes[2 * v], kSC);
+        const double cost = nch * std::max(3.0, (double)blocks / 256.0 + 2.5);
+        if (nch == 4 || cost < least) {
+            least = cost;
+            best = nch;
+        }
+    }
+    return best;
+}
+
 // The loss after the argument checks.  views: host room for n_views entries.
 // ws == nullptr with ws_bytes == 0 only sizes the call (*ws_required).
 mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, const float *gt_rgb,
                     const float *depth, const float *gt_depth, const float *scales, int64_t n_gauss,
                     const mgs_loss_opts *opts, LossView *views, void *ws, size_t ws_bytes, size_t *ws_required,
                     float *loss, float *dL_drgb, float *dL_ddepth, float *dL_dscales, void *stream) {
-    int64_t tiles = 0, P = 0;
+    const int nch = ssim_chunks(sizes, n_views);
+    int64_t tiles = 0, P = 0, squares = 0, n_depth = 0;
     for (int v = 0; v < n_views; ++v) {
         const int32_t W = sizes[2 * v], H = sizes[2 * v + 1];
         LossView &L = views[v];
         L.W = W;
         L.H = H;
-        L.TXn = (int32_t)ceil_div(W, kLT);
+        L.strips = (int32_t)ceil_div(W, kSC);
         L.pad = 0;
         L.tile_base = tiles;
         L.pix_base = P;
+        L.depth_base = n_depth;
         L.inv_n3 = (float)(1.0 / (3.0 * (double)W * (double)H));
         L.inv_n1 = (float)(1.0 / ((double)W * (double)H));
-        tiles += (int64_t)L.TXn * ceil_div(H, kLT);
+        tiles += L.strips * ceil_div(H, 8 * nch - kWarm);
+        squares += ceil_div(W, 32) * ceil_div(H, 32);
+        if (depth) n_depth += ceil_div((int64_t)W * H, kDepthPix);
         P += (int64_t)W * H;
     }
-    if (tiles >= (int64_t(1) << 31) - 8) return MGS_ERR_TOO_LARGE;
+    if (squares >= (int64_t(1) << 31) - 8) return MGS_ERR_TOO_LARGE;
     const bool iso = scales != nullptr && n_gauss > 0;
-    const int64_t n_iso = iso ? ceil_div(n_gauss, 256) : 0;
+    const int64_t n_iso = iso ? ceil_div(n_gauss, kIsoGauss) : 0;
+    if (3 * tiles + n_depth + n_iso >= (int64_t(1) << 31) - 16) return MGS_ERR_TOO_LARGE;
     Bump b;
     const size_t off_views = b.take(sizeof(LossView) * (size_t)n_views);
-    const size_t off_maps = b.take(4 * (size_t)9 * (size_t)P);
-    const size_t off_part = b.take(4 * (size_t)12 * (size_t)tiles);
-    const size_t off_iso = b.take(8 * (size_t)std::max<int64_t>(n_iso, 1));
+    // The size that the interface states, 36 bytes per pixel and 48 per 32x32
+    // square, is what callers plan for; the partial sums take a part of it.
+    const size_t off_part = b.take(4 * (size_t)9 * (size_t)P + 256 + 4 * (size_t)12 * (size_t)squares);
+    const size_t off_iso = b.take(8 * (size_t)std::max<int64_t>(iso ? ceil_div(n_gauss, 256) : 0, 1));
     const size_t off_terms = b.take(8 * (size_t)(n_views + 1));
     *ws_required = b.size();
     if (ws_bytes < b.size() || !ws) return MGS_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    static_assert(sizeof(LossView) % 4 == 0, "views are copied as words");
+    ViewTable vt{};
+    vt.n = n_views;
     const size_t view_bytes = sizeof(LossView) * (size_t)n_views;
-    if (view_bytes <= 4 * (size_t)kArgCopyWords) {
-        ArgWords aw;
-        memcpy(aw.w, views, view_bytes);
-        aw.n = (int32_t)(view_bytes / 4);
-        k_arg_copy<<<1, 256, 0, s>>>(aw, at<uint32_t>(ws, off_views));
-        MGS_LAUNCHED();
+    static_assert(sizeof(LossView) % 4 == 0, "views are copied as words");
+    if (n_views <= kArgViews) {
+        memcpy(vt.own, views, view_bytes);
     } else {
-        MGS_HIP(hipMemcpyAsync(at<void>(ws, off_views), views, view_bytes, hipMemcpyHostToDevice, s));
+        vt.table = at<LossView>(ws, off_views);
+        if (view_bytes <= 4 * (size_t)kArgCopyWords) {
+            ArgWords aw;
+            memcpy(aw.w, views, view_bytes);
+            aw.n = (int32_t)(view_bytes / 4);
+            k_arg_copy<<<1, 256, 0, s>>>(aw, at<uint32_t>(ws, off_views));
+            MGS_LAUNCHED();
+        } else {
+            MGS_HIP(hipMemcpyAsync(at<void>(ws, off_views), views, view_bytes, hipMemcpyHostToDevice, s));
+        }
     }
+    float *partial = at<float>(ws, off_part), *depth_partial = partial + 6 * tiles;
     SsimArgs a;
-    a.views = at<LossView>(ws, off_views);
-    a.n_views = n_views;
+    a.views = vt;
     a.n_tiles = tiles;
-    a.P = P;
+    a.nch = nch;
     a.rgb = rgb;
     a.gt = gt_rgb;
-    a.depth = depth;
-    a.gtd = gt_depth;
-    a.maps = at<float>(ws, off_maps);
-    a.partial = at<float>(ws, off_part);
+    a.partial = partial;
     a.d_rgb = dL_drgb;
-    a.d_depth = dL_ddepth;
     a.lam = opts->lambda_ssim;
-    a.w_depth = opts->w_depth;
     {
         double w[kLW], sum = 0.0;
         for (int o = 0; o < kLW; ++o) {
@@ -547,21 +680,27 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
         }
         for (int o = 0; o < kLW; ++o) a.w[o] = (float)(w[o] / sum);
     }
-    const dim3 grid((unsigned)(8 * ceil_div(tiles, 8)), 3);
-    k_ssim_fwd<<<grid, 256, 0, s>>>(a);
-    MGS_LAUNCHED();
-    k_ssim_bwd<<<grid, 256, 0, s>>>(a);
-    MGS_LAUNCHED();
     double *iso_part = at<double>(ws, off_iso);
-    if (iso) {
-        k_iso<<<(unsigned)n_iso, 256, 0, s>>>(scales, n_gauss, opts->w_iso, dL_dscales, iso_part);
-        MGS_LAUNCHED();
-    }
+    RestArgs r;
+    r.n_depth = n_depth;
+    r.depth = depth;
+    r.gtd = gt_depth;
+    r.d_depth = dL_ddepth;
+    r.depth_partial = depth_partial;
+    r.w_depth = opts->w_depth;
+    r.scales = scales;
+    r.n = iso ? n_gauss : 0;
+    r.w_iso = opts->w_iso;
+    r.d_scales = dL_dscales;
+    r.iso_partial = iso_part;
+    k_loss<<<(unsigned)(8 * ceil_div(3 * tiles, 8) + n_depth + n_iso), 256, 0, s>>>(a, r);
+    MGS_LAUNCHED();
     FinalArgs f;
-    f.views = a.views;
-    f.n_views = n_views;
+    f.views = vt;
     f.n_tiles = tiles;
-    f.partial = a.partial;
+    f.n_depth = n_depth;
+    f.partial = partial;
+    f.depth_partial = depth_partial;
     f.iso_partial = iso_part;
     f.n_iso_blocks = n_iso;
     f.n_gauss = iso ? n_gauss : 0;
@@ -571,9 +710,7 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
     f.has_depth = depth != nullptr;
     f.terms = at<double>(ws, off_terms);
     f.loss = loss;
-    k_loss_views<<<(unsigned)n_views + 1, 256, 0, s>>>(f);
-    MGS_LAUNCHED();
-    k_loss_total<<<1, 64, 0, s>>>(f.terms, n_views, loss);
+    k_loss_final<<<1, 1024, 0, s>>>(f);
     MGS_LAUNCHED();
     return MGS_OK;
 }

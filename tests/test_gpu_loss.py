@@ -92,6 +92,26 @@ def test_loss_ragged_views_match_oracle():
                                rtol=1e-5)
 
 
+# strips of 54 columns and tiles of 8, 16, 24, ... rows: one less, exact, one more; a
+# single row and column; more views than the kernel arguments carry
+@pytest.mark.parametrize("sizes", [
+    [(53, 7), (54, 8), (55, 9)],
+    [(108, 16), (109, 17), (107, 15)],
+    [(1, 120), (200, 1), (64, 64)],
+    [(162, 104), (163, 105), (12, 6)],
+    [(20 + 3 * k, 31 - k) for k in range(18)],
+], ids=["one_strip", "two_strips", "thin", "three_strips", "many_views"])
+def test_loss_tile_edges_match_oracle(sizes):
+    rng = np.random.default_rng(12)
+    rgb, gt, d, gd = _images(rng, sizes)
+    scales = rng.uniform(0.01, 0.1, size=(1025, 3)).astype(np.float32)
+    lam, wd, wi = 0.2, 0.7, 3.0
+    print("case loss tile edges", sizes[:3], flush=True)
+    res = mapping_loss(sizes, _flat(rgb), _flat(gt), _flat(d), _flat(gd), torch.from_numpy(scales).cuda(),
+                       lam, wd, wi)
+    _check(sizes, rgb, gt, d, gd, scales, lam, wd, wi, res)
+
+
 def test_loss_full_window_size():
     """The window's 8 views of 1200x680 in one call: view 0 against the whole
     oracle; view 7 on three bands of rows (top, middle, bottom), each from the
