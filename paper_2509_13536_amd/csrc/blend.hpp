@@ -615,16 +615,12 @@ struct BlendBwdArgs {
     uint32_t *queues;
     const float *out_T, *dL_rgb, *dL_depth;
     const uint32_t *n_contrib;
-    float *records;  // [M][10]
+    float *records;  // [M][10], written where some pixel visited the entry
+    uint8_t *live;   // [M] cleared before: 1 where the record is written
     int box_cull;    // as in BlendArgs
     const uint16_t *inst_qm;  // the forward's quadrant masks per list entry (bins of several tiles; nullable)
 };
 
-__device__ __forceinline__ void zero_record(float *records, uint32_t e) {
-    float2 *rec = reinterpret_cast<float2 *>(records + (int64_t)e * kRecord);
-#pragma unroll
-    for (int c = 0; c < kRecord / 2; ++c) rec[c] = make_float2(0.f, 0.f);
-}
 // The kRecord = 10 per-lane values of one Gaussian visit are summed over the
 // 64 lanes in two stages.
 //  (1) wave_fold_record folds them with the CDNA4 cross-row swaps:
@@ -772,9 +768,9 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
             ncq[i] = uniform_u32(wave_max_u32(nc[i]));
             ncmax = ncq[i] > ncmax ? ncq[i] : ncmax;
         }
+        // Gaussians past every pixel's last contributor get no record, nor do
+        // those that no quadrant visits.
         const uint2 rg = a.range[item];
-        // Gaussians past every pixel's last contributor get zero records.
-        for (uint32_t s = rg.x + ncmax + lane; s < rg.y; s += 64) zero_record(a.records, a.inst.slot(s, a.inst.key[s]));
         int hi = (int)ncmax;
         while (hi > 0) {
             const int lo = hi > 64 ? hi - 64 : 0;
@@ -797,8 +793,6 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
                 if (qm) {
                     cd = a.rrgbd[k];
                     if (may_clamp(xy.x, xy.y, cn, t.qx0[0], t.qx1[QX - 1], t.qy0[0], t.qy1[G::QY - 1])) qm |= kClampBit;
-                } else {
-                    zero_record(a.records, e);
                 }
             }
             const uint64_t m = ballot(qm != 0);
@@ -829,6 +823,7 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
                     if (POSE && src < 0) r = 0.0f;
                     const uint32_t js = (uint32_t)(pend >> (6 * ff)) & 63u;
                     a.records[(int64_t)sh.e[js] * kRecord + fv] = r;
+                    if (fv == 0) a.live[sh.e[js]] = 1;
                 }
                 __syncthreads();  // sh.part may be written again
             };
@@ -846,8 +841,7 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
                 for (int i = 0; i < NQ; ++i)
                     if (slot_pos < ncq[i]) slot_live |= qm & (1u << i);
             }
-            // the staged Gaussians that some quadrant visits; the others get
-            // zero records
+            // the staged Gaussians that some quadrant visits
             const uint64_t visited = ballot(slot_live != 0);
             // the visit loop, without the clamp when no staged Gaussian of the
             // batch can reach it
@@ -971,8 +965,6 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
             if (batch_clamp) visits(std::true_type{});
             else visits(std::false_type{});
             if (nfold) flush(nfold);
-            // staged Gaussians that no pixel of the bin reached: zero records
-            if (lane < nlive && !((visited >> lane) & 1ull)) zero_record(a.records, sh.e[lane]);
             __syncthreads();
             hi = lo;
         }
@@ -1066,9 +1058,6 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
         __syncthreads();
         const uint32_t ncmax = max(max(sh.ncq[0], sh.ncq[1]), max(sh.ncq[2], sh.ncq[3]));
         const uint2 rg = a.range[item];
-        // Gaussians past every pixel's last contributor get zero records.
-        for (uint32_t s = rg.x + ncmax + threadIdx.x; s < rg.y; s += 256)
-            zero_record(a.records, a.inst.slot(s, a.inst.key[s]));
         int hi = (int)ncmax;
         while (hi > 0) {
             const int lo = hi > 64 ? hi - 64 : 0;
@@ -1090,8 +1079,6 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
                     if (qm) {
                         cd = a.rrgbd[k];
                         if (may_clamp(xy.x, xy.y, cn, tb.qx0[0], tb.qx1[QX - 1], tb.qy0[0], tb.qy1[QX - 1])) qm |= kClampBit;
-                    } else {
-                        zero_record(a.records, e);
                     }
                 }
                 const uint64_t m = ballot(qm != 0);
@@ -1188,15 +1175,18 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
             if (nfold) flush(nfold);
             if (lane == 0) sh.folded[w] = visited;
             __syncthreads();
-            // records: the four waves' values in wave order; zeros for a staged
-            // Gaussian that no pixel of the bin reached
+            // records: the four waves' values in wave order, for the staged
+            // Gaussians that some wave visited
+            const uint64_t any = (sh.folded[0] | sh.folded[1]) | (sh.folded[2] | sh.folded[3]);
             for (int o = threadIdx.x; o < nlive * kRecord; o += 256) {
                 const int j = o / kRecord, vv = o - j * kRecord;
+                if (!((any >> j) & 1ull)) continue;
                 float r = 0.0f;
 #pragma unroll
                 for (int ww = 0; ww < 4; ++ww)
                     if ((sh.folded[ww] >> j) & 1ull) r += sh.rec[j][ww][vv];
                 a.records[(int64_t)sh.e[j] * kRecord + vv] = r;
+                if (vv == 0) a.live[sh.e[j]] = 1;
             }
             __syncthreads();
             hi = lo;

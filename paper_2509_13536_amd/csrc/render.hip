@@ -89,6 +89,14 @@ __global__ void k_setup(SetupArgs a, ViewDev *views, MapDev *maps, int32_t *vlis
     copy_words(a.vlist, vlist, a.n_views);
 }
 
+// The backward's start: its counters, and no record live yet.
+__global__ __launch_bounds__(256) void k_bwd_init(uint32_t *counters, uint4 *live, int64_t n16) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < CNT_WORDS; i += blockDim.x) counters[i] = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (int64_t)gridDim.x * 256)
+        live[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -719,8 +727,8 @@ __global__ __launch_bounds__(256) void k_tile_ranges(const uint32_t *half, uint3
 // ---------------------------------------------------------------- per-rank record sums
 // One row of 16 lanes per depth rank: the rank's records are contiguous
 // (emission order), the row strides over them and reduces with DPP.
-__global__ __launch_bounds__(256) void k_rank_reduce(const float *records, const uint32_t *rank_off, int64_t Pv,
-                                                     float *grad2d) {
+__global__ __launch_bounds__(256) void k_rank_reduce(const float *records, const uint8_t *live, const uint32_t *rank_off,
+                                                     int64_t Pv, float *grad2d) {
     const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
     const int sub = threadIdx.x & 15;
     float acc[kRecord];
@@ -729,6 +737,7 @@ __global__ __launch_bounds__(256) void k_rank_reduce(const float *records, const
     if (k < Pv) {
         const uint32_t e0 = rank_off[k], e1 = rank_off[k + 1];
         for (uint32_t e = e0 + sub; e < e1; e += 16) {
+            if (!live[e]) continue;
             const float2 *rec = reinterpret_cast<const float2 *>(records + (int64_t)e * kRecord);
 #pragma unroll
             for (int c = 0; c < kRecord / 2; ++c) {
@@ -1094,7 +1103,7 @@ struct Layout {
         scan_tmp_pre, n_contrib, n_blend, blk_vis, blk_cnt, blk_kmin, blk_kmax, pre_size;
     // post-count
     size_t sk0, sk1, sv0, sv1, rank_off, rank_xy, rank_conic, rank_rgbd, rank_rect, it0, it1, iv0, iv1, hist,
-        scan_tmp, tile_range, bin_order, records, grad2d, pair_grad, pose_partial, inst_qm, total;
+        scan_tmp, tile_range, bin_order, records, grad2d, pair_grad, pose_partial, inst_qm, live, total;
     int64_t pose_blocks;  // pair-backward blocks per map
     int grad_stride;      // floats per pair gradient
 };
@@ -1160,11 +1169,12 @@ Layout make_layout(const Setup &S, int64_t Pv, int64_t M, bool bwd) {
     if (bwd) {
         L.records = b.take(4 * kRecord * M);
         L.inst_qm = b.take(2 * M);  // the forward's quadrant mask per list entry
+        L.live = b.take((M + 15) / 16 * 16);  // which records a backward wrote
         L.grad2d = b.take(4 * kRecord * Pv);
         L.pair_grad = b.take(4 * (size_t)L.grad_stride * Pv);
         L.pose_partial = b.take(4 * 9 * V * NM * L.pose_blocks);
     } else {
-        L.records = L.grad2d = L.pair_grad = L.pose_partial = L.inst_qm = 0;
+        L.records = L.grad2d = L.pair_grad = L.pose_partial = L.inst_qm = L.live = 0;
     }
     L.total = b.size();
     return L;
@@ -1546,7 +1556,9 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     StageTimer timer(opts, s);
     timer.mark();  // 0
     uint32_t *counters = at<uint32_t>(ws, L.counters);
-    k_init<<<1, 64, 0, s>>>(counters);
+    const int64_t live16 = (M + 15) / 16;
+    k_bwd_init<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(live16, 256), 1024)), 256, 0, s>>>(
+        counters, at<uint4>(ws, L.live), live16);
     const ViewDev *views = at<ViewDev>(ws, L.views);
     const mgs_render_opts defaults{};
     const mgs_render_opts &o = opts ? *opts : defaults;
@@ -1568,6 +1580,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     bb.dL_depth = dL_ddepth;
     bb.n_contrib = at<uint32_t>(ws, L.n_contrib);
     bb.records = at<float>(ws, L.records);
+    bb.live = at<uint8_t>(ws, L.live);
     bb.box_cull = box_cull();
     bb.inst_qm = !split_blend(S.btx, S.bty, S.B_total) && S.btx * S.bty > 1 ? at<uint16_t>(ws, L.inst_qm) : nullptr;
     // tracking: no map asks for any Gaussian gradient or statistic
@@ -1590,7 +1603,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     timer.mark();  // 1
     // per-pair chain rule, then per-Gaussian sums over views, then the poses
     float *grad2d = at<float>(ws, L.grad2d);
-    if (Pv > 0) k_rank_reduce<<<grid_of(16 * Pv, 256), 256, 0, s>>>(bb.records, at<uint32_t>(ws, L.rank_off), Pv, grad2d);
+    if (Pv > 0) k_rank_reduce<<<grid_of(16 * Pv, 256), 256, 0, s>>>(bb.records, bb.live, at<uint32_t>(ws, L.rank_off), Pv, grad2d);
     MGS_LAUNCHED();
     float *partial = at<float>(ws, L.pose_partial);
     float *pair_grad = at<float>(ws, L.pair_grad);
