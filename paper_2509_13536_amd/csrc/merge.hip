@@ -396,13 +396,14 @@ __device__ __forceinline__ void load_gs(const float *means, const float *scales,
     gs_of(r, o);
 }
 
-__device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, const float *sj, float *q_out,
-                         float *s_out);
+__device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, const float *sj, bool second,
+                         float *q_out, float *s_out);
 
 // G_k from G_i (older) and G_j (Eqs. (6), (9), (10)); result replaces i.
-// LBFGS: Eq. (9) by the paper's iterative solver instead of its closed form.
+// LBFGS: Eq. (9) by the paper's iterative solver instead of its closed form, on
+// a pair of neighbouring lanes that hold the same values (second: the odd one).
 template <bool LBFGS>
-__device__ void merge_pair(Gs &i, const Gs &j) {
+__device__ void merge_pair(Gs &i, const Gs &j, bool second = false) {
     MGS_CONTRACT
     // Eq. (6), written around mu_i: mu_k = mu_i + (P_i + P_j)^-1 P_j (mu_j - mu_i)
     const float *Pi = i.P, *Pj = j.P;
@@ -420,7 +421,7 @@ __device__ void merge_pair(Gs &i, const Gs &j) {
     const float x2 = (c02 * b[0] + c12 * b[1] + c22 * b[2]) * id;
     if constexpr (LBFGS) {
         float qk[4], sk[3];
-        w2_lbfgs(i.q, i.s, j.q, j.s, qk, sk);
+        w2_lbfgs(i.q, i.s, j.q, j.s, second, qk, sk);
         i.mu[0] += x0; i.mu[1] += x1; i.mu[2] += x2;
         for (int k = 0; k < 4; ++k) i.q[k] = qk[k];
         for (int k = 0; k < 3; ++k) i.s[k] = sk[k];
@@ -540,6 +541,15 @@ __device__ void merge_pair(Gs &i, const Gs &j) {
 // quaternion.  Memory 4, Armijo backtracking, stop at a largest gradient entry
 // of 1e-6 (about 1e-6 relative in Sigma_k) or after kLbfgsIters iterations
 // (about 7 on the test room; up to 91 where the pair's frames differ most).
+//
+// The solve is one dependent chain of fp64 operations a voxel, bound by their
+// latency, with most of the chip idle.  Two lanes share it: each decomposes the
+// inner matrix of one of the two covariances, and they exchange the results, so
+// both hold the same state, bit for bit what one lane would (a path of up to 128
+// iterations amplifies a rounding, so no operation changes); the stored steps
+// are in registers (constant indices); and a wave takes as few voxels as the chip
+// has room for, since it lasts as long as its slowest.  100k Gaussians: 5.3 ->
+// 1.9 ms.
 constexpr int kLbfgsMem = 4;
 constexpr int kLbfgsIters = 128;
 
@@ -547,15 +557,49 @@ struct D3 {
     double a[9];
 };
 
+// a / b and sqrt(x), correctly rounded as the operators are, without their
+// scaling of extreme exponents and their special cases: for finite operands of
+// exponents within +-400, x positive.  Newton steps on the hardware's estimates,
+// then the residual (Markstein): 8 and 9 instructions instead of 11 and 17.
+__device__ __forceinline__ double div_mid(double a, double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+    r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+    const double q = a * r;
+    return __builtin_fma(__builtin_fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double sqrt_mid(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, e, g);
+    h = __builtin_fma(h, e, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+// x of the pair's other lane
+__device__ __forceinline__ double pair_other(double x) {
+    const int2 v = __builtin_bit_cast(int2, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, v.x, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
+    const int hi = __builtin_amdgcn_update_dpp(0, v.y, 0xB1, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, make_int2(lo, hi));
+}
+
 __device__ void jacobi3_d(D3 A, double *lam, D3 &V) {
     double a00 = A.a[0], a01 = A.a[1], a02 = A.a[2], a11 = A.a[4], a12 = A.a[5], a22 = A.a[8];
 #pragma unroll
     for (int i = 0; i < 9; ++i) V.a[i] = (i % 4 == 0) ? 1.0 : 0.0;
     auto rot = [&](double &app, double &aqq, double &apq, double &arp, double &arq, int p, int q) {
         if (apq == 0.0) return;
-        const double theta = (aqq - app) / (2.0 * apq);
-        const double t = copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
+        double t;
+        if (fabs(apq) > 1e-40) {  // |theta| below 1e50 (the entries are of order one)
+            const double theta = div_mid(aqq - app, 2.0 * apq);
+            t = div_mid(copysign(1.0, theta), fabs(theta) + sqrt_mid(theta * theta + 1.0));
+        } else {
+            const double theta = (aqq - app) / (2.0 * apq);
+            t = copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
+        }
+        const double c = div_mid(1.0, sqrt_mid(t * t + 1.0)), s = t * c;
         const double tapq = t * apq;
         app -= tapq;
         aqq += tapq;
@@ -592,51 +636,50 @@ __device__ __forceinline__ D3 rot_of_d(const double *q) {  // unit (w, x, y, z)
     return R;
 }
 
-// Eq. (9) objective at x = (q[4], s[3]) and its gradient g[7]; Si, Sj are the
-// pair's covariances in the scaled units, world frame.
-__device__ double w2_objective(const double *x, const D3 &Si, const D3 &Sj, double *g) {
+// Eq. (9) objective at x = (q[4], s[3]) and its gradient g[7]; S is the lane's
+// covariance of the pair's two (second: the other Gaussian's) in the scaled
+// units, world frame.  Both lanes add the first lane's terms, then the second's.
+__device__ double w2_objective(const double *x, const D3 &S, bool second, double *g) {
     const double nq = sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3]);
     const double qh[4] = {x[0] / nq, x[1] / nq, x[2] / nq, x[3] / nq};
     const double sk[3] = {x[4], x[5], x[6]};
     const D3 R = rot_of_d(qh);
-    double f = 2.0 * (sk[0] * sk[0] + sk[1] * sk[1] + sk[2] * sk[2]);
-    double G[9] = {2, 0, 0, 0, 2, 0, 0, 0, 2};  // d f / d Sigma_k in G_k's frame
-    for (int w = 0; w < 2; ++w) {
-        const D3 &S = w ? Sj : Si;
-        double RS[9];  // R^T S
+    double RS[9];  // R^T S
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
-                RS[3 * i + j] = R.a[i] * S.a[j] + R.a[3 + i] * S.a[3 + j] + R.a[6 + i] * S.a[6 + j];
-        D3 inner;  // diag(s) R^T S R diag(s)
-        double trA = 0.0;
+        for (int j = 0; j < 3; ++j)
+            RS[3 * i + j] = R.a[i] * S.a[j] + R.a[3 + i] * S.a[3 + j] + R.a[6 + i] * S.a[6 + j];
+    D3 inner;  // diag(s) R^T S R diag(s)
+    double trA = 0.0;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double A = RS[3 * i] * R.a[j] + RS[3 * i + 1] * R.a[3 + j] + RS[3 * i + 2] * R.a[6 + j];
-                if (i == j) trA += A;
-                inner.a[3 * i + j] = sk[i] * A * sk[j];
-            }
+        for (int j = 0; j < 3; ++j) {
+            const double A = RS[3 * i] * R.a[j] + RS[3 * i + 1] * R.a[3 + j] + RS[3 * i + 2] * R.a[6 + j];
+            if (i == j) trA += A;
+            inner.a[3 * i + j] = sk[i] * A * sk[j];
+        }
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = i + 1; j < 3; ++j) inner.a[3 * i + j] = inner.a[3 * j + i] = 0.5 * (inner.a[3 * i + j] + inner.a[3 * j + i]);
-        double lam[3];
-        D3 V;
-        jacobi3_d(inner, lam, V);
-        const double r[3] = {sqrt(fmax(lam[0], 0.0)), sqrt(fmax(lam[1], 0.0)), sqrt(fmax(lam[2], 0.0))};
-        f += trA - 2.0 * (r[0] + r[1] + r[2]);
+        for (int j = i + 1; j < 3; ++j) inner.a[3 * i + j] = inner.a[3 * j + i] = 0.5 * (inner.a[3 * i + j] + inner.a[3 * j + i]);
+    double lam[3];
+    D3 V;
+    jacobi3_d(inner, lam, V);
+    const double r[3] = {sqrt(fmax(lam[0], 0.0)), sqrt(fmax(lam[1], 0.0)), sqrt(fmax(lam[2], 0.0))};
+    const double fm = trA - 2.0 * (r[0] + r[1] + r[2]), fo = pair_other(fm);
+    const double f = (2.0 * (sk[0] * sk[0] + sk[1] * sk[1] + sk[2] * sk[2]) + (second ? fo : fm)) + (second ? fm : fo);
+    double G[9];  // d f / d Sigma_k in G_k's frame
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double root = V.a[3 * i] * r[0] * V.a[3 * j] + V.a[3 * i + 1] * r[1] * V.a[3 * j + 1] +
-                                    V.a[3 * i + 2] * r[2] * V.a[3 * j + 2];
-                G[3 * i + j] -= root / (sk[i] * sk[j]);
-            }
-    }
+        for (int j = 0; j < 3; ++j) {
+            const double root = V.a[3 * i] * r[0] * V.a[3 * j] + V.a[3 * i + 1] * r[1] * V.a[3 * j + 1] +
+                                V.a[3 * i + 2] * r[2] * V.a[3 * j + 2];
+            const double gm = root / (sk[i] * sk[j]), go = pair_other(gm);
+            G[3 * i + j] = ((i == j ? 2.0 : 0.0) - (second ? go : gm)) - (second ? gm : go);
+        }
     // d f / d s_c = 2 s_c G_cc; d f / d R = 2 R G diag(s^2)
     for (int c = 0; c < 3; ++c) g[4 + c] = 2.0 * sk[c] * G[4 * c];
     double F[9];
@@ -662,24 +705,21 @@ __device__ double w2_objective(const double *x, const D3 &Si, const D3 &Sj, doub
 
 // (q_k, s_k) minimising Eq. (9) for the pair (qi, si), (qj, sj) (unit quaternions,
 // world frame), from the Eq. (10) start.
-__device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, const float *sj, float *q_out,
-                         float *s_out) {
+__device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, const float *sj, bool second,
+                         float *q_out, float *s_out) {
     const double sigma = (si[0] + si[1] + si[2] + sj[0] + sj[1] + sj[2]) / 6.0;
-    D3 Si, Sj;
+    D3 Sw;  // this lane's covariance
     {
-        const double qa[4] = {qi[0], qi[1], qi[2], qi[3]}, qb[4] = {qj[0], qj[1], qj[2], qj[3]};
-        const D3 Ra = rot_of_d(qa), Rb = rot_of_d(qb);
-        const double da[3] = {si[0] / sigma, si[1] / sigma, si[2] / sigma};
-        const double db[3] = {sj[0] / sigma, sj[1] / sigma, sj[2] / sigma};
+        double q[4], d[3];
+        for (int k = 0; k < 4; ++k) q[k] = second ? qj[k] : qi[k];
+        for (int k = 0; k < 3; ++k) d[k] = (second ? sj[k] : si[k]) / sigma;
+        const D3 R = rot_of_d(q);
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                Si.a[3 * i + j] = Ra.a[3 * i] * da[0] * da[0] * Ra.a[3 * j] + Ra.a[3 * i + 1] * da[1] * da[1] * Ra.a[3 * j + 1] +
-                                  Ra.a[3 * i + 2] * da[2] * da[2] * Ra.a[3 * j + 2];
-                Sj.a[3 * i + j] = Rb.a[3 * i] * db[0] * db[0] * Rb.a[3 * j] + Rb.a[3 * i + 1] * db[1] * db[1] * Rb.a[3 * j + 1] +
-                                  Rb.a[3 * i + 2] * db[2] * db[2] * Rb.a[3 * j + 2];
-            }
+            for (int j = 0; j < 3; ++j)
+                Sw.a[3 * i + j] = R.a[3 * i] * d[0] * d[0] * R.a[3 * j] + R.a[3 * i + 1] * d[1] * d[1] * R.a[3 * j + 1] +
+                                  R.a[3 * i + 2] * d[2] * d[2] * R.a[3 * j + 2];
     }
     // Eq. (10) averages the scales axis by axis, which presumes corresponding
     // axes: of G_j's 24 equivalent (q, s) take the one whose frame is nearest
@@ -712,9 +752,17 @@ __device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, cons
         for (int c = 0; c < 3; ++c) x[4 + c] = (0.5 * ((double)si[c] + (double)sa[c]) + delta[c]) / sigma;
     }
     double g[7];
-    double f = w2_objective(x, Si, Sj, g);
+    double f = w2_objective(x, Sw, second, g);
+    // the last steps and gradient differences, newest first (in registers: every
+    // index below is a constant)
     double S[kLbfgsMem][7], Y[kLbfgsMem][7], rho[kLbfgsMem];
-    int nmem = 0, head = 0;
+#pragma unroll
+    for (int u = 0; u < kLbfgsMem; ++u) {
+        rho[u] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) S[u][k] = Y[u][k] = 0.0;
+    }
+    int nmem = 0;
     for (int it = 0; it < kLbfgsIters; ++it) {
         double gmax = 0.0;
         for (int k = 0; k < 7; ++k) gmax = fmax(gmax, fabs(g[k]));
@@ -722,30 +770,32 @@ __device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, cons
         // two-loop recursion: d = -H g
         double qv[7], al[kLbfgsMem];
         for (int k = 0; k < 7; ++k) qv[k] = g[k];
-        for (int u = 0; u < nmem; ++u) {
-            const int b = (head - 1 - u + kLbfgsMem) % kLbfgsMem;
+#pragma unroll
+        for (int u = 0; u < kLbfgsMem; ++u) {
+            al[u] = 0.0;
+            if (u >= nmem) continue;
             double a = 0.0;
-            for (int k = 0; k < 7; ++k) a += S[b][k] * qv[k];
-            a *= rho[b];
+            for (int k = 0; k < 7; ++k) a += S[u][k] * qv[k];
+            a *= rho[u];
             al[u] = a;
-            for (int k = 0; k < 7; ++k) qv[k] -= a * Y[b][k];
+            for (int k = 0; k < 7; ++k) qv[k] -= a * Y[u][k];
         }
         double gam;
         if (nmem > 0) {
-            const int b = (head - 1 + kLbfgsMem) % kLbfgsMem;
             double sy = 0.0, yy = 0.0;
-            for (int k = 0; k < 7; ++k) { sy += S[b][k] * Y[b][k]; yy += Y[b][k] * Y[b][k]; }
+            for (int k = 0; k < 7; ++k) { sy += S[0][k] * Y[0][k]; yy += Y[0][k] * Y[0][k]; }
             gam = sy / yy;
         } else {
             gam = 1e-2 / gmax;
         }
         for (int k = 0; k < 7; ++k) qv[k] *= gam;
-        for (int u = nmem - 1; u >= 0; --u) {
-            const int b = (head - 1 - u + kLbfgsMem) % kLbfgsMem;
+#pragma unroll
+        for (int u = kLbfgsMem - 1; u >= 0; --u) {
+            if (u >= nmem) continue;
             double bb = 0.0;
-            for (int k = 0; k < 7; ++k) bb += Y[b][k] * qv[k];
-            bb *= rho[b];
-            for (int k = 0; k < 7; ++k) qv[k] += S[b][k] * (al[u] - bb);
+            for (int k = 0; k < 7; ++k) bb += Y[u][k] * qv[k];
+            bb *= rho[u];
+            for (int k = 0; k < 7; ++k) qv[k] += S[u][k] * (al[u] - bb);
         }
         double d[7], gd = 0.0;
         for (int k = 0; k < 7; ++k) { d[k] = -qv[k]; gd += g[k] * d[k]; }
@@ -759,21 +809,28 @@ __device__ void w2_lbfgs(const float *qi, const float *si, const float *qj, cons
         bool ok = false;
         for (int ls = 0; ls < 30; ++ls) {
             for (int k = 0; k < 7; ++k) xn[k] = x[k] + t * d[k];
-            fn = w2_objective(xn, Si, Sj, gn);
+            fn = w2_objective(xn, Sw, second, gn);
             if (fn <= f + 1e-4 * t * gd) { ok = true; break; }
             t *= 0.5;
         }
         if (!ok) break;  // no decrease left at fp64 resolution
-        double sy = 0.0;
+        double sv[7], yv[7], sy = 0.0;
         for (int k = 0; k < 7; ++k) {
-            S[head][k] = xn[k] - x[k];
-            Y[head][k] = gn[k] - g[k];
-            sy += S[head][k] * Y[head][k];
+            sv[k] = xn[k] - x[k];
+            yv[k] = gn[k] - g[k];
+            sy += sv[k] * yv[k];
         }
         if (sy > 1e-300) {
-            rho[head] = 1.0 / sy;
-            head = (head + 1) % kLbfgsMem;
+#pragma unroll
+            for (int u = kLbfgsMem - 1; u > 0; --u) {
+                rho[u] = rho[u - 1];
+                for (int k = 0; k < 7; ++k) { S[u][k] = S[u - 1][k]; Y[u][k] = Y[u - 1][k]; }
+            }
+            rho[0] = 1.0 / sy;
+            for (int k = 0; k < 7; ++k) { S[0][k] = sv[k]; Y[0][k] = yv[k]; }
             nmem = nmem < kLbfgsMem ? nmem + 1 : kLbfgsMem;
+        } else if (nmem == kLbfgsMem) {  // no curvature along the step: it takes the oldest one's place, its rho stays
+            for (int k = 0; k < 7; ++k) { S[kLbfgsMem - 1][k] = sv[k]; Y[kLbfgsMem - 1][k] = yv[k]; }
         }
         for (int k = 0; k < 7; ++k) { x[k] = xn[k]; g[k] = gn[k]; }
         f = fn;
@@ -883,16 +940,30 @@ struct VoxelArgs {
 // chains in one wave cost the diverging lanes' work and their extra
 // residents on every step of it.  The other voxels follow 64 to a wave (dense,
 // so the lanes all merge, along chains of one length).
+// LBFGS: a voxel takes two neighbouring lanes, and a wave as few voxels (2 to 32)
+// as 4096 waves can hold them all in: a wave lasts as long as its slowest voxel,
+// and four to a SIMD one after another even that out (100k Gaussians: 2.67 ms
+// with 512 waves, 2.81 with 1024, 2.24 with 2048, 1.81 with 4096, 3.21 with 8192).
+constexpr int64_t kLbfgsWaves = 4096;
+__device__ __forceinline__ int lbfgs_voxels(int64_t nvox) {
+    int v = 2;
+    while (v < 32 && v * kLbfgsWaves < nvox) v *= 2;
+    return v;
+}
 template <class K, bool LBFGS>
 __global__ __launch_bounds__(64) void k_voxels(VoxelArgs<K> a) {
+    constexpr int kLanes = LBFGS ? 2 : 1;
     const int64_t nlong = min((int64_t)*a.nlong, a.long_waves);
+    const bool second = LBFGS && (threadIdx.x & 1);
     int64_t t;
     if ((int64_t)blockIdx.x < a.long_waves) {
-        if (threadIdx.x != 0 || (int64_t)blockIdx.x >= nlong) return;
+        if (threadIdx.x >= kLanes || (int64_t)blockIdx.x >= nlong) return;
         t = blockIdx.x;
         __builtin_amdgcn_s_setprio(3);
     } else {
-        t = nlong + ((int64_t)blockIdx.x - a.long_waves) * 64 + threadIdx.x;
+        const int per = LBFGS ? lbfgs_voxels((int64_t)*a.nvox) : 64;
+        if ((int)threadIdx.x >= per * kLanes) return;
+        t = nlong + ((int64_t)blockIdx.x - a.long_waves) * per + threadIdx.x / kLanes;
         if (t >= (int64_t)*a.nvox) return;
     }
     const int64_t i = a.order[t];
@@ -933,7 +1004,7 @@ __global__ __launch_bounds__(64) void k_voxels(VoxelArgs<K> a) {
                 Gs B;
                 if (best == 0) B = R0;
                 else B = R[best];
-                merge_pair<LBFGS>(B, J);  // one merge site: the merge is long code
+                merge_pair<LBFGS>(B, J, second);  // one merge site: the merge is long code
                 if (best == 0) R0 = B;
                 else R[best] = B;
                 a.alive[gj] = 0u;
@@ -969,7 +1040,7 @@ __global__ __launch_bounds__(64) void k_voxels(VoxelArgs<K> a) {
         if (bi >= 0 && bd < a.chi2) {
             Gs B = R[bi];
             const Gs J = R[bj];
-            merge_pair<LBFGS>(B, J);
+            merge_pair<LBFGS>(B, J, second);
             const uint32_t gi = a.gids[i + bi], gj = a.gids[i + bj];
             a.alive[gj] = 0u;
             a.merged[gi] = 1u;
@@ -1081,9 +1152,10 @@ hipError_t sort_and_merge(void *ws, const MergeLayout &L, const int32_t *hb, int
     VoxelArgs<K> va{in->means, in->scales, in->quats, keys[cur], vals[cur], ne, order, count + 2, book,
                     long_waves, chi2, policy, at<Gs>(ws, L.res), alive, merged, at<float>(ws, L.new_mu),
                     at<float>(ws, L.new_q), at<float>(ws, L.new_s)};
-    const unsigned vgrid = (unsigned)(long_waves + ceil_div(ne, 64));
-    if (policy & MGS_MERGE_LBFGS) k_voxels<K, true><<<vgrid, 64, 0, s>>>(va);
-    else k_voxels<K, false><<<vgrid, 64, 0, s>>>(va);
+    // at most ne / 2 voxels: ne / 64 waves of 32, or kLbfgsWaves of fewer
+    if (policy & MGS_MERGE_LBFGS)
+        k_voxels<K, true><<<(unsigned)(long_waves + std::max<int64_t>(ceil_div(ne, 64), kLbfgsWaves)), 64, 0, s>>>(va);
+    else k_voxels<K, false><<<(unsigned)(long_waves + ceil_div(ne, 64)), 64, 0, s>>>(va);
     return hipGetLastError();
 }
 }  // namespace

@@ -173,3 +173,34 @@ def test_lbfgs_solver_matches_the_closed_form():
           f"worst objective excess {worst_obj:.2e}", flush=True)
     assert worst <= 1e-4, worst
     assert n_single > 50
+
+
+def test_lbfgs_solver_is_the_same_at_every_packing():
+    """A wave takes 2 to 32 voxels by the call's number of voxels, and long
+    voxels take waves of their own: a voxel's result has the same bits whether
+    its call merges 38k voxels, half or a fiftieth of them (the others masked)."""
+    rng = np.random.default_rng(3)
+    n = 120_000
+    means = rng.uniform(0.0, 2.0, size=(n, 3))
+    means[:40] = 0.01 + 0.03 * rng.uniform(size=(40, 3))  # a long voxel
+    q = rng.normal(size=(n, 4))
+    sc = synth.Scene(means.astype(np.float32), rng.uniform(0.01, 0.06, size=(n, 3)).astype(np.float32),
+                     q.astype(np.float32), np.full(n, 0.5, np.float32), np.zeros((n, 1, 3), np.float32), 0)
+    m = GaussianMap.from_numpy(sc)
+    cells, ok = M.voxel_cells(sc.means, 0.05, np.ones(n, bool))
+    part = (cells[:, 0] * 7 + cells[:, 1] * 5 + cells[:, 2]) % 50
+
+    def merged(mask):
+        print(f"case lbfgs packing, {int(mask.sum())} eligible", flush=True)
+        r = voxel_merge(m, torch.from_numpy(mask.astype(np.uint8)).cuda(), voxel_size=0.05, solver="lbfgs")
+        o2n = r.old_to_new.cpu().numpy()
+        vals = np.concatenate([getattr(r.map, k).cpu().numpy() for k in ("means", "scales", "quats")], axis=1)
+        return o2n >= 0, vals[np.maximum(o2n, 0)]
+
+    alive, vals = merged(ok)
+    assert 1000 < n - alive.sum()
+    for mask in (ok & (part < 25), ok & (part == 7), ok & (part == part[0])):
+        a, v = merged(mask)
+        assert np.array_equal(a[mask], alive[mask])
+        keep = mask & alive
+        assert np.array_equal(v[keep], vals[keep])
