@@ -97,6 +97,45 @@ __global__ __launch_bounds__(256) void k_bin_place(const uint2 *range, int64_t n
     }
 }
 
+// Both in one launch of one block, for calls with few bins (four a thread, their
+// lists' lengths kept in registers).  3225 bins of one 1200x680 view: 4.7 us
+// against 4.7 + 4.7 us, and 300 bins 2.3 us against 2.2 + 3.4; four bins a thread
+// is as far as the registers were taken, beyond that the two launches stay.
+constexpr int64_t kBinOrderOneBlock = 4096;
+__global__ __launch_bounds__(1024) void k_bin_order(const uint2 *range, int n, uint32_t *order) {
+    __shared__ uint32_t h[kOrderClasses];
+    __shared__ uint32_t sums[4];
+    constexpr int kPer = (int)(kBinOrderOneBlock / 1024);
+    if (threadIdx.x < kOrderClasses) h[threadIdx.x] = 0;
+    __syncthreads();
+    uint2 r[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + 1024 * k;
+        r[k] = i < n ? range[i] : make_uint2(0u, 0u);
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if ((int)threadIdx.x + 1024 * k < n) atomicAdd(&h[len_class(r[k].y - r[k].x)], 1u);
+    __syncthreads();
+    // the classes' first slots
+    const uint32_t c = threadIdx.x < kOrderClasses ? h[threadIdx.x] : 0u;
+    const uint32_t incl = wave_incl_scan_u32(c);
+    if (threadIdx.x < kOrderClasses && lane_id() == 63) sums[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    if (threadIdx.x < kOrderClasses) {
+        uint32_t before = incl - c;
+        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) before += sums[w];
+        h[threadIdx.x] = before;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + 1024 * k;
+        if (i < n) order[atomicAdd(&h[len_class(r[k].y - r[k].x)], 1u)] = (uint32_t)i;
+    }
+}
+
 // Slot of queue q's next bin in the order (queue q takes slots q, q + 8, ...);
 // -1 once all eight queues are empty.
 __device__ __forceinline__ int64_t next_item(uint32_t *queues, int64_t n_items, int &q, int &tries) {

@@ -1,5 +1,6 @@
-// Exclusive prefix sums over uint32 values (three launches: per-block sums,
-// scan of the block sums in one block, per-block scan with the block prefix).
+// Exclusive prefix sums over uint32 values: per-block sums, then a per-block scan
+// that adds up the sums of the blocks before it itself; of more than
+// kScanDirectBlocks blocks, a launch between the two scans the block sums.
 // Load/Store are device functors, so a scan can gather its input and scatter
 // its output (used for stream compaction and for the per-rank tile counts).
 #pragma once
@@ -67,12 +68,30 @@ static __global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t *sums
     }
 }
 
-template <class Load, class Store>
+// sum of v over the block, in every thread
+__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t *lds4) {
+    v = wave_sum_u32(v);
+    if (lane_id() == 0) lds4[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const uint32_t t = (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
+    __syncthreads();
+    return t;
+}
+
+// DIRECT: sums are the block sums (the last block also writes the grand total);
+// else their exclusive scan.
+template <class Load, class Store, bool DIRECT>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(Load load, Store store, int64_t n,
-                                                            const uint32_t *prefix) {
+                                                            const uint32_t *sums, uint32_t *total) {
     __shared__ uint32_t lds[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    uint32_t carry = prefix[blockIdx.x];
+    uint32_t carry = 0;
+    if constexpr (DIRECT) {
+        for (unsigned i = threadIdx.x; i < blockIdx.x; i += kScanThreads) carry += sums[i];
+        carry = block_sum_u32(carry, lds);
+    } else {
+        carry = sums[blockIdx.x];
+    }
     for (int r = 0; r < kScanRounds; ++r) {
         const int64_t i = base + r * kScanThreads + threadIdx.x;
         const uint32_t v = i < n ? load(i) : 0u;
@@ -81,7 +100,15 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(Load load, Store sto
         if (i < n) store(i, carry + ex, v);
         carry += tot;
     }
+    if (DIRECT && total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = carry;
 }
+
+// A block of a direct scan reads up to this many sums, four a thread, from L2.
+// The scan of 725 thousand values (354 blocks): 6.2 us for k_scan_down against
+// 5.8 + 3.2 us for it and k_scan_top, and at every size one launch's gap less
+// (3-6 us in a short chain).  The line lies where the mean read, half of this,
+// would reach the top launch's cost by that slope (0.4 us for 354 sums).
+constexpr int64_t kScanDirectBlocks = 1024;
 
 inline int64_t scan_tmp_words(int64_t n) { return ceil_div(n, kScanTile) + 1; }
 
@@ -91,9 +118,13 @@ inline hipError_t scan_exclusive(Load load, Store store, int64_t n, uint32_t *tm
                                  hipStream_t s) {
     const int64_t nb = ceil_div(n, kScanTile);
     if (nb > 0) k_scan_reduce<Load><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(load, n, tmp);
+    if (nb > 0 && nb <= kScanDirectBlocks) {
+        k_scan_down<Load, Store, true><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(load, store, n, tmp, total);
+        return hipGetLastError();
+    }
     k_scan_top<<<1, kScanThreads, 0, s>>>(tmp, nb, total);
     if (nb > 0)
-        k_scan_down<Load, Store><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(load, store, n, tmp);
+        k_scan_down<Load, Store, false><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(load, store, n, tmp, nullptr);
     return hipGetLastError();
 }
 

@@ -473,3 +473,28 @@ def test_wide_and_packed_instances_agree(bins, size, monkeypatch):
     for k in gr_p[0]:
         assert torch.equal(gr_p[0][k], gr_w[0][k]), k
     assert torch.equal(pose_p, pose_w)
+
+
+@pytest.mark.parametrize("n,W,H,n_views,bins", [(2000, 1024, 1024, 1, 4096), (2000, 1024, 1025, 1, 4160),
+                                                (400_000, 96, 64, 8, 192)])
+def test_bin_order_and_scan_paths(n, W, H, n_views, bins, monkeypatch):
+    """Calls of up to 4096 bins order them in one block, larger ones in two
+    launches; scans of up to 2^21 values add their block sums up themselves,
+    larger ones launch a kernel for it.  On either side of the lines an image is
+    the oracle's, and a view among several equals the view alone."""
+    monkeypatch.setenv("MGS_BIN_TILES", "1x1")
+    sc = synth.tiny_scene(n, W, H, 47, log_scale_mu=-3.0 if n < 10_000 else -5.5)
+    print(f"case {n} Gaussians, {W}x{H}, {n_views} views", flush=True)
+    m = GaussianMap.from_numpy(sc)
+    view = View.from_camera(sc.cams[0], 0)
+    st = render_forward([m], [view] * n_views)
+    assert n_views * ((W + 15) // 16) * ((H + 15) // 16) == bins
+    if n_views == 1:
+        image_parity(sc, sc.cams[0], st)
+        return
+    assert int(st.info.n_visible) > 1 << 21
+    alone = render_forward([m], [view])
+    torch.cuda.synchronize()
+    for v in range(n_views):
+        for x, y in zip(st.view_images(v), alone.view_images(0)):
+            assert torch.equal(x, y), v
