@@ -573,6 +573,76 @@ struct SideRankCount {
     }
 };
 
+// The pair sort of a one-view call with few visible pairs, in one launch: a
+// pair's rank is the number of pairs whose key is smaller, or equal and earlier.
+// A block ranks 32 pairs; each half of its 16 waves, a lane a pair, compares them
+// with 1/32 of the keys, which it first brings to LDS.  Bound by the launch and
+// three dependent memory accesses for few pairs, by the compares (two
+// instructions for 64 of them) for many: 13 us for 8.2 thousand pairs and 22 us
+// for 15 thousand, where three byte passes take nine launches of 3-4 us and the
+// time between them.  The line: a 10k-Gaussian view goes from 120 to 101 us by
+// it, 15 thousand visible pairs from 260 to 246 us; the compares grow with the
+// square, the passes hardly, and meet near 20 thousand.  Views are not compared,
+// so it takes one view.
+constexpr int64_t kRankByCountingMax = 16384;
+constexpr int kRankWaves = 16, kRankParts = 2 * kRankWaves, kRankStep = 16;
+constexpr int kRankPerPart = (int)(kRankByCountingMax / kRankParts);
+__global__ __launch_bounds__(64 * kRankWaves) void k_rank_pairs(const uint32_t *keys, const uint32_t *vals, int n,
+                                                                const uint32_t *pair_count, uint32_t *rank_pair,
+                                                                uint32_t *rank_count) {
+    // the two parts of a wave are read at once: four words apart modulo the banks
+    __shared__ uint4 lkeys[kRankParts][kRankPerPart / 4 + 1];
+    __shared__ uint32_t ranks[kRankParts][32];
+    const int item = (int)threadIdx.x & 31, part = (int)threadIdx.x >> 5;
+    const int i0 = (int)blockIdx.x * 32, i = i0 + item;
+    const uint32_t key = i < n ? keys[i] : 0u;
+    const int steps = (n + kRankStep - 1) / kRankStep, per = (steps + kRankParts - 1) / kRankParts * kRankStep;
+    const int j0 = part * per;
+    uint32_t *mine = reinterpret_cast<uint32_t *>(lkeys[part]);
+    constexpr int kLoads = kRankPerPart / 32;
+    uint32_t k[kLoads];
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) {
+        const int q = 32 * r + item;
+        k[r] = q < per && j0 + q < n ? keys[j0 + q] : 0xFFFFFFFFu;  // counted by no pair
+    }
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) mine[32 * r + item] = k[r];
+    __builtin_amdgcn_wave_barrier();
+    uint32_t rank = 0;
+    for (int q = 0; q < per; q += kRankStep) {
+        uint4 c[kRankStep / 4];
+#pragma unroll
+        for (int t = 0; t < kRankStep / 4; ++t) c[t] = lkeys[part][q / 4 + t];
+        const int j = j0 + q;
+        // earlier keys count when equal too; keys are below 2^32 - 1.  i0 and j are
+        // multiples of the step, so only a step inside the block's own 32 has both kinds.
+        const uint32_t bound = key + (j < i0 ? 1u : 0u);
+#pragma unroll
+        for (int t = 0; t < kRankStep; ++t) {
+            const uint32_t kj = t & 2 ? (t & 1 ? c[t / 4].w : c[t / 4].z) : (t & 1 ? c[t / 4].y : c[t / 4].x);
+            rank += kj < bound ? 1u : 0u;
+        }
+        if (j >= i0 && j < i0 + 32) {
+#pragma unroll
+            for (int t = 0; t < kRankStep; ++t) {
+                const uint32_t kj = t & 2 ? (t & 1 ? c[t / 4].w : c[t / 4].z) : (t & 1 ? c[t / 4].y : c[t / 4].x);
+                rank += kj == key && j + t < i ? 1u : 0u;
+            }
+        }
+    }
+    ranks[part][item] = rank;
+    __syncthreads();
+    if (threadIdx.x < 32 && i < n) {
+        uint32_t r = 0;
+#pragma unroll
+        for (int w = 0; w < kRankParts; ++w) r += ranks[w][item];
+        const uint32_t pair = vals[i];
+        rank_pair[r] = pair;
+        rank_count[r] = pair_count[pair];
+    }
+}
+
 struct EmitArgs {
     const ViewDev *views;
     int n_views;
@@ -1448,7 +1518,14 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
         uint32_t kmin = host_cnt[CNT_KMIN], kmax = host_cnt[CNT_KMAX];
         if (kmax < kmin) kmin = 0, kmax = 0xFFFFFFFFu;  // not expected with Pv > 0: the full key range
         const int kbits = bits_for((int64_t)kmax - (int64_t)kmin + 1);
-        const int passes = (kbits + bits_for(n_views) + 7) / 8;
+        const bool counting = n_views == 1 && Pv <= kRankByCountingMax && kmax != 0xFFFFFFFFu;
+        if (counting) {
+            k_rank_pairs<<<(unsigned)ceil_div(Pv, 32), 64 * kRankWaves, 0, s>>>(
+                sk[0], sv[0], (int)Pv, pa.pair_count, sv[1], at<uint32_t>(ws, L.rank_off));
+            counts_in_rank_order = true;
+            cur = 1;
+        }
+        const int passes = counting ? 0 : (kbits + bits_for(n_views) + 7) / 8;
         for (int p = 0; p < passes; ++p) {
             const PairDigit dig{pa.views, n_views, kmin, kbits, 8 * p};
             if (p + 1 < passes) {
@@ -1465,7 +1542,9 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     info->off_rank_pair = cur ? L.sv1 : L.sv0;
     // instance offsets in rank order
     uint32_t *rank_off = at<uint32_t>(ws, L.rank_off);
-    if (counts_in_rank_order)  // in place
+    if (counts_in_rank_order && Pv <= kScanOneBlock)  // in place
+        k_scan_one<<<1, 1024, 0, s>>>(rank_off, (int)Pv, rank_off + Pv);
+    else if (counts_in_rank_order)
         MGS_HIP(scan_exclusive(LoadU32{rank_off}, StoreU32{rank_off}, Pv, tmp, rank_off + Pv, s));
     else
         MGS_HIP(scan_exclusive(LoadRankCount{rank_pair, pa.pair_count}, StoreU32{rank_off}, Pv, tmp, rank_off + Pv, s));

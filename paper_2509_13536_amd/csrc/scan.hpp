@@ -137,4 +137,55 @@ struct StoreU32 {
     __device__ void operator()(int64_t i, uint32_t ex, uint32_t) const { p[i] = ex; }
 };
 
+// In-place scan of few values in one launch of one block (four a thread and
+// round, all loads in flight), and their total.  p is 16-byte aligned.  Bound by
+// the chain of load, wave scan and store: 4.4 us for 8 to 15 thousand values,
+// against 3.6 + 5.3 us and a launch's gap for k_scan_reduce and k_scan_down.
+constexpr int64_t kScanOneBlock = 16384;
+static __global__ __launch_bounds__(1024) void k_scan_one(uint32_t *p, int n, uint32_t *total) {
+    constexpr int kRounds = (int)(kScanOneBlock / 4096);
+    __shared__ uint32_t sums[kRounds][16];
+    const int i0 = 4 * (int)threadIdx.x, wave = (int)threadIdx.x >> 6;
+    uint4 v[kRounds];
+    uint32_t ex[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int i = 4096 * r + i0;
+        if (i + 4 <= n) {
+            v[r] = *reinterpret_cast<const uint4 *>(p + i);
+        } else {
+            v[r].x = i < n ? p[i] : 0u;
+            v[r].y = i + 1 < n ? p[i + 1] : 0u;
+            v[r].z = i + 2 < n ? p[i + 2] : 0u;
+            v[r].w = 0u;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t sum = (v[r].x + v[r].y) + (v[r].z + v[r].w), incl = wave_incl_scan_u32(sum);
+        ex[r] = incl - sum;
+        if (lane_id() == 63) sums[r][wave] = incl;
+    }
+    __syncthreads();
+    uint32_t carry = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        uint32_t o = carry + ex[r];
+        for (int w = 0; w < 16; ++w) {
+            o += w < wave ? sums[r][w] : 0u;
+            carry += sums[r][w];
+        }
+        const uint4 e = make_uint4(o, o + v[r].x, o + v[r].x + v[r].y, o + v[r].x + v[r].y + v[r].z);
+        const int i = 4096 * r + i0;
+        if (i + 4 <= n) {
+            *reinterpret_cast<uint4 *>(p + i) = e;
+        } else {
+            if (i < n) p[i] = e.x;
+            if (i + 1 < n) p[i + 1] = e.y;
+            if (i + 2 < n) p[i + 2] = e.z;
+        }
+    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
 }  // namespace mgs

@@ -498,3 +498,21 @@ def test_bin_order_and_scan_paths(n, W, H, n_views, bins, monkeypatch):
     for v in range(n_views):
         for x, y in zip(st.view_images(v), alone.view_images(0)):
             assert torch.equal(x, y), v
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 511, 4097, 16384])
+def test_rank_by_counting(n):
+    """One-view calls of up to 16384 visible pairs count each pair's rank.  Half
+    of the Gaussians share one of four depths; every bin's list, which holds its
+    pairs in depth order and equal depths in index order, is the oracle's."""
+    sc = synth.tiny_scene(n, 64, 48, 53, log_scale_mu=-5.0)
+    rng = np.random.default_rng(n)
+    means = sc.means.copy()
+    same = rng.random(n) < 0.5
+    means[same, 2] = rng.choice(np.float32([1.5, 2.0, 2.25, 2.75]), n)[same]
+    means[:, :2] *= 0.6
+    sc = synth.Scene(means, sc.scales, sc.quats, sc.opac, sc.sh, sc.sh_degree, sc.cams, f"ranks{n}")
+    print(f"case {n} pairs", flush=True)
+    st = run_forward(sc)
+    assert n // 2 <= int(st.info.n_visible) <= 16384
+    assert_keys_and_lists(sc, sc.cams[0], st)
