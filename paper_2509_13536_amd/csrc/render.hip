@@ -33,7 +33,8 @@
 //   k_rank_reduce  per rank: the sum of its records (contiguous)
 //   k_pair_bwd     per visible pair: chain rule to the Gaussian's parameters,
 //                  block partial sums of the pose gradient
-//   k_gauss_bwd    per Gaussian: its pairs summed over views in view order
+//   k_gauss_bwd, k_gauss_bwd_sh3
+//                  per Gaussian: its pairs summed over views in view order
 //   k_pose_final   fp64 reduction of the pose partials
 #include <algorithm>
 #include <cmath>
@@ -1004,6 +1005,125 @@ __global__ __launch_bounds__(256) void k_gauss_bwd(GaussBwdArgs a) {
     }
 }
 
+// The same at degree 3, whose rows of 59 floats a thread alone would write as
+// many short pieces.  A block takes 64 Gaussians and keeps their pairs' ranks of
+// up to kGaussViews views in LDS; then its threads walk the output arrays in
+// memory order, four SH floats each, so that a wave writes whole lines, with all
+// loads of a view in flight.  Bound by the writes, most of them zeros for the
+// Gaussians that no tile holds (708 MB for 3M Gaussians: 104 us at a fill's
+// rate) and the chain count, rank, row, store of each block: 253 -> 184 us.  At
+// degree 0 (8 views of 500k) the 14-float rows are faster a thread each, 29
+// against 40 us, so the lower degrees stay above.
+constexpr int kGaussBlock = 64, kGaussViews = 8;
+constexpr uint32_t kNoRank = 0xFFFFFFFFu;
+
+// This thread's items tid, tid + 256, ... (of VEC floats) of the block's part of
+// a W-wide output array, whose rows are columns col.. of the pairs' gradient rows.
+template <int VEC>
+struct __attribute__((packed, aligned(4))) FloatsU {
+    float x[VEC];
+};
+template <int W, int VEC>
+struct GaussItems {
+    static constexpr int kItems = kGaussBlock * W / VEC, kEach = (kItems + 255) / 256, kRow = W / VEC;
+    FloatsU<VEC> acc[kEach], t[kEach];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int r = 0; r < kEach; ++r)
+            for (int c = 0; c < VEC; ++c) acc[r].x[c] = 0.0f;
+    }
+    __device__ __forceinline__ void load(const uint32_t (&ranks)[kGaussBlock], const float *pair_grad, int stride,
+                                         int col) {
+#pragma unroll
+        for (int r = 0; r < kEach; ++r) {
+            const int e = 256 * r + (int)threadIdx.x, g = e / kRow;
+            const uint32_t k = kItems % 256 == 0 || e < kItems ? ranks[g] : kNoRank;
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) t[r].x[c] = 0.0f;
+            if (k != kNoRank)
+                t[r] = *reinterpret_cast<const FloatsU<VEC> *>(pair_grad + (int64_t)k * stride + col +
+                                                               VEC * (e - g * kRow));
+        }
+    }
+    __device__ __forceinline__ void add() {  // 0 where there is no pair: acc is never -0
+#pragma unroll
+        for (int r = 0; r < kEach; ++r)
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) acc[r].x[c] += t[r].x[c];
+    }
+    __device__ __forceinline__ void store(float *out, int64_t g0, int64_t n) const {
+        if (!out) return;
+        const int64_t end = (n - g0) * kRow;
+#pragma unroll
+        for (int r = 0; r < kEach; ++r) {
+            const int e = 256 * r + (int)threadIdx.x;
+            if (e < kItems && e < end) reinterpret_cast<FloatsU<VEC> *>(out + g0 * W)[e] = acc[r];
+        }
+    }
+};
+
+__global__ __launch_bounds__(256) void k_gauss_bwd_sh3(GaussBwdArgs a) {
+    constexpr int K = 16;
+    __shared__ uint32_t ranks[kGaussViews][kGaussBlock];
+    const int64_t n = a.maps[a.map].n, g0 = (int64_t)blockIdx.x * kGaussBlock;
+    const int gl = (int)threadIdx.x & (kGaussBlock - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGaussBlock);
+    const bool mine = g0 + gl < n;
+    const bool stats = a.gr.grad_norm_sum != nullptr;
+    GaussItems<3 * K, 4> sh;
+    GaussItems<3, 1> means, scales;
+    GaussItems<4, 1> quats;
+    GaussItems<1, 1> opac;
+    sh.clear();
+    means.clear();
+    scales.clear();
+    quats.clear();
+    opac.clear();
+    // Eq. (3) statistics: per view that keeps the Gaussian after culling, the
+    // norm of that view's mean gradient (0 when no tile list holds it)
+    float norm_sum = 0.0f;
+    uint32_t seen = 0;
+    for (int v0 = 0; v0 < a.n_map_views; v0 += kGaussViews) {
+        const int nv = std::min(a.n_map_views - v0, kGaussViews);
+        if (v0) __syncthreads();
+        for (int v = w; v < nv; v += 256 / kGaussBlock) {
+            const int64_t p = a.views[a.view_list[v0 + v]].pair_base + g0 + gl;
+            const uint32_t cnt = mine ? a.pair_count[p] : 0u, k = mine ? a.pair_rank[p] : 0u;
+            ranks[v][gl] = cnt != 0 ? k : kNoRank;  // no tile list holds the pair
+        }
+        __syncthreads();
+        for (int v = 0; v < nv; ++v) {  // all of a view's loads are in flight together
+            sh.load(ranks[v], a.pair_grad, a.stride, kPairGradFixed);
+            means.load(ranks[v], a.pair_grad, a.stride, 0);
+            scales.load(ranks[v], a.pair_grad, a.stride, 3);
+            quats.load(ranks[v], a.pair_grad, a.stride, 6);
+            opac.load(ranks[v], a.pair_grad, a.stride, 10);
+            sh.add();
+            means.add();
+            scales.add();
+            quats.add();
+            opac.add();
+        }
+        if (stats && w == 0 && mine)
+            for (int v = 0; v < nv; ++v) {
+                if (a.pair_depth[a.views[a.view_list[v0 + v]].pair_base + g0 + gl] != 0xFFFFFFFFu) ++seen;
+                const uint32_t k = ranks[v][gl];
+                if (k == kNoRank) continue;
+                const float *src = a.pair_grad + (int64_t)k * a.stride;
+                norm_sum += sqrtf(src[0] * src[0] + src[1] * src[1] + src[2] * src[2]);
+            }
+    }
+    if (stats && w == 0 && mine) {
+        a.gr.grad_norm_sum[g0 + gl] += norm_sum;
+        a.gr.visible_count[g0 + gl] += seen;
+    }
+    sh.store(a.gr.d_sh, g0, n);
+    means.store(a.gr.d_means, g0, n);
+    scales.store(a.gr.d_scales, g0, n);
+    quats.store(a.gr.d_quats, g0, n);
+    opac.store(a.gr.d_opac, g0, n);
+}
+
 struct PoseFinalArgs {
     const ViewDev *views;
     int n_views;
@@ -1776,7 +1896,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
             case 0: k_gauss_bwd<0><<<nbg, 256, 0, s>>>(ga); break;
             case 1: k_gauss_bwd<1><<<nbg, 256, 0, s>>>(ga); break;
             case 2: k_gauss_bwd<2><<<nbg, 256, 0, s>>>(ga); break;
-            default: k_gauss_bwd<3><<<nbg, 256, 0, s>>>(ga); break;
+            default: k_gauss_bwd_sh3<<<grid_of(S.maps[m].n, kGaussBlock), 256, 0, s>>>(ga); break;
         }
         MGS_LAUNCHED();
     }

@@ -12,7 +12,7 @@ import torch
 
 import oracle
 import synth
-from paper_2509_13536_amd import GaussianMap, View, render_backward, render_forward
+from paper_2509_13536_amd import GaussianMap, GradStats, View, render_backward, render_forward
 
 from gpu_helpers import _inst_lists, assert_keys_and_lists, grad_parity, image_parity, run_forward
 
@@ -516,3 +516,34 @@ def test_rank_by_counting(n):
     st = run_forward(sc)
     assert n // 2 <= int(st.info.n_visible) <= 16384
     assert_keys_and_lists(sc, sc.cams[0], st)
+
+
+@pytest.mark.parametrize("n,n_views", [(63, 1), (64, 8), (129, 9)])
+def test_degree3_gradients_over_views(n, n_views):
+    """Degree-3 gradients are gathered 64 Gaussians a block, eight views at a
+    time: block edges and a second group of views, with the statistics, against
+    the oracle's sum over views."""
+    sc = synth.tiny_scene(n, 60, 44, 59, sh_degree=3, log_scale_mu=-2.8)
+    cams = []
+    for v in range(n_views):
+        T = sc.cams[0].Tcw.copy()
+        T[0, 3] += 0.15 * (v - n_views // 2)  # some Gaussians leave some views
+        c = sc.cams[0]
+        cams.append(synth.Camera(c.W, c.H, c.fx, c.fy, c.cx, c.cy, T))
+    sc.cams[:] = cams
+    print(f"case {n} Gaussians, {n_views} views", flush=True)
+    st = run_forward(sc, need_backward=True)
+    g_rgb, g_d = synth.upstream_grads(cams, 5)
+    for v, cam in enumerate(cams):
+        amb = oracle.forward(sc, cam)["amb"]
+        g_rgb[v][:, amb] = 0
+        g_d[v][amb] = 0
+    stats = GradStats.zeros(n)
+    grads, _ = render_backward(st, torch.from_numpy(np.concatenate([g.reshape(-1) for g in g_rgb])).cuda(),
+                               torch.from_numpy(np.concatenate([g.reshape(-1) for g in g_d])).cuda(), stats=[stats])
+    refs = [oracle.backward(sc, cam, g_rgb[v], g_d[v]) for v, cam in enumerate(cams)]
+    for name in ("means", "scales", "quats", "opac", "sh"):
+        grad_parity(grads[0][name].cpu().numpy(), sum(r[name] for r in refs), name)
+    ref_sum, ref_cnt = oracle.grad_stats(sc, cams, g_rgb, g_d)
+    assert np.array_equal(stats.visible_count.cpu().numpy(), ref_cnt)
+    grad_parity(stats.grad_norm_sum.cpu().numpy(), ref_sum, "grad_norm_sum")
