@@ -1178,8 +1178,8 @@ struct Setup {
 // holds twice the pixel state (3 waves per SIMD in the backward, 4 in the
 // forward), so the bins must outnumber the resident waves several times over.
 // Calls with at least kBin2x1FromTiles tiles therefore take 2 x 1 bins (the
-// window: 2.25 -> 2.18 ms per step), smaller ones 1 x 1 (below kSplitBelowBins
-// bins also split into quadrant waves).  2 x 2 bins hold 4x the state and are
+// window: 2.25 -> 2.18 ms per step), smaller ones 1 x 1 (few bins
+// also split into quadrant waves).  2 x 2 bins hold 4x the state and are
 // slower (about 18 % on the window).  MGS_BIN_TILES = "1x1", "2x1" or "2x2"
 // forces a size.
 constexpr int64_t kBin2x1FromTiles = 16384;
@@ -1275,17 +1275,25 @@ bool box_cull() {
     return e && !strcmp(e, "box");
 }
 
-// A forward call with fewer bins than this splits each 16x16 bin into its four
-// quadrants, one wave each (k_blend_fwd SPLIT): four times the waves, one
-// evaluation per visit, the same bits.  MGS_BLEND_SPLIT=0 or 1 forces either.
-constexpr int64_t kSplitBelowBins = 4096;
-bool split_blend(int btx, int bty, int64_t n_bins) {
+// A call with few bins splits each 16x16 bin into its four quadrants, one wave
+// each: four times the waves, one evaluation per visit, in the forward the same
+// bits (k_blend_fwd SPLIT, k_blend_bwd_split).  MGS_BLEND_SPLIT=0 or 1 forces
+// either.  While the bins hardly outnumber the resident waves (6144), the longest
+// list alone sets the time.  Forward calls, one wave a bin against four, us: 4800
+// bins of a room of 500k Gaussians 477 / 384, of a surface 925 / 849; 6450 bins
+// 356 / 337, 730 / 558 with 1M, 538 / 543; 7200 bins 547 / 484, 1231 / 1190; 9675
+// bins 401 / 412, 818 / 719, 720 / 741; 12900 bins 451 / 489, 893 / 930.  The
+// split backward pays for four staged copies of each list and a fold over the
+// waves; from a split forward on, forward and backward together: 4800 bins 892 /
+// 832, 1670 / 1890; 6450 bins 661 / 668, 1004 / 1152; 9675 bins 794 / 903.
+constexpr int64_t kSplitFwdBelowBins = 8192, kSplitBwdBelowBins = 4096;
+bool split_blend(int btx, int bty, int64_t n_bins, int64_t below) {
     if (btx != 1 || bty != 1) return false;
     if (const char *e = getenv("MGS_BLEND_SPLIT")) {
         if (e[0] == '0') return false;
         if (e[0] == '1') return true;
     }
-    return n_bins < kSplitBelowBins;
+    return n_bins < below;
 }
 
 void launch_blend_fwd(bool count, bool split, int btx, int bty, unsigned grid, hipStream_t s, const BlendArgs &ba) {
@@ -1755,7 +1763,7 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     ba.out_T = out_T;
     ba.n_contrib = at<uint32_t>(ws, L.n_contrib);
     ba.n_blend = at<uint32_t>(ws, L.n_blend);
-    const bool split = split_blend(S.btx, S.bty, S.B_total);
+    const bool split = split_blend(S.btx, S.bty, S.B_total, kSplitFwdBelowBins);
     // the one-wave forward of a backward call over bins of several tiles keeps
     // its quadrant masks for the backward (the same bins, the same decisions)
     ba.inst_qm = bwd && !split && S.btx * S.bty > 1 ? at<uint16_t>(ws, L.inst_qm) : nullptr;
@@ -1821,7 +1829,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     bb.records = at<float>(ws, L.records);
     bb.live = at<uint8_t>(ws, L.live);
     bb.box_cull = box_cull();
-    bb.inst_qm = !split_blend(S.btx, S.bty, S.B_total) && S.btx * S.bty > 1 ? at<uint16_t>(ws, L.inst_qm) : nullptr;
+    bb.inst_qm = S.btx * S.bty > 1 ? at<uint16_t>(ws, L.inst_qm) : nullptr;
     // tracking: no map asks for any Gaussian gradient or statistic
     bool pose_only = true;
     for (int m = 0; m < n_maps; ++m) {
@@ -1834,7 +1842,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     for (int m = 0; m < n_maps; ++m)
         if (S.maps[m].sh_degree != 0) pose_blend = false;
     // few bins: four-wave blocks, one per bin, five to a CU (their LDS)
-    const bool split = split_blend(S.btx, S.bty, S.B_total);
+    const bool split = split_blend(S.btx, S.bty, S.B_total, kSplitBwdBelowBins);
     const int64_t grid = split ? std::max<int64_t>(1, std::min<int64_t>(S.B_total, (int64_t)num_cus() * 5))
                                : blend_grid(S.B_total);
     launch_blend_bwd(split, S.btx, S.bty, (unsigned)grid, s, bb, pose_blend);

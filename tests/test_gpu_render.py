@@ -547,3 +547,24 @@ def test_degree3_gradients_over_views(n, n_views):
     ref_sum, ref_cnt = oracle.grad_stats(sc, cams, g_rgb, g_d)
     assert np.array_equal(stats.visible_count.cpu().numpy(), ref_cnt)
     grad_parity(stats.grad_norm_sum.cpu().numpy(), ref_sum, "grad_norm_sum")
+
+
+@pytest.mark.parametrize("W,H", [(1024, 1024), (1024, 2032), (1024, 2048)])
+def test_split_forward_with_either_backward(W, H, monkeypatch):
+    """Between 4096 and 8192 bins the forward is split and the backward is not;
+    the split forward's images are the one-wave forward's, and so are the
+    gradients that the one-wave backward forms from them."""
+    sc = synth.tiny_scene(3000, W, H, 61, log_scale_mu=-3.0)
+    print(f"case {W}x{H}", flush=True)
+    m = GaussianMap.from_numpy(sc)
+    g = torch.randn(3 * W * H, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    out = []
+    for forced in (None, "0"):
+        if forced is not None:
+            monkeypatch.setenv("MGS_BLEND_SPLIT", forced)
+        st = render_forward([m], [View.from_camera(sc.cams[0], 0)], need_backward=True)
+        grads, d_pose = render_backward(st, g)
+        torch.cuda.synchronize()
+        out.append((st.rgb, st.depth, st.T, d_pose, *[grads[0][k] for k in ("means", "scales", "quats", "opac", "sh")]))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
