@@ -94,3 +94,23 @@ def test_many_keypoints():
     torch.cuda.synchronize()
     exp = PG.patch_grid_sample(kf.cam, kf.keypoints, kf.kp_depth, kf.image, None, P=16, min_kp=6, s=2)
     _compare(kf, res, exp, len(kf.keypoints))
+
+
+@pytest.mark.parametrize("W,H,patch,samples,n_kp", [(512, 256, 8, 2, 8192), (512, 256, 8, 2, 8193),
+                                                    (1024, 513, 8, 1, 100), (80, 64, 16, 2, 176), (80, 64, 16, 2, 177)])
+def test_launch_variants_match_oracle(W, H, patch, samples, n_kp):
+    """Either side of the lines of the one-launch forms: 8192 keypoints or patches
+    counted by one block, 16384 candidates written without a scan, and a last
+    block of 256 candidates that is full or holds one."""
+    rng = np.random.default_rng(n_kp)
+    cam = synth.Camera(W, H, 0.8 * W, 0.8 * W, W / 2.0, H / 2.0, np.eye(4, dtype=np.float32)[:3].copy())
+    kp = rng.uniform(0, 1, (n_kp, 2)) ** 2 * [W, H]
+    kp = kp.astype(np.float32)
+    kd = np.where(rng.uniform(size=n_kp) < 0.9, rng.uniform(1, 3, n_kp), 0).astype(np.float32)
+    image = rng.uniform(0, 1, (3, H, W)).astype(np.float32)
+    print(f"case {W}x{H} patch {patch}, {n_kp} keypoints", flush=True)
+    res = patch_grid_sample(View.from_camera(cam), _t(kp), _t(kd), _t(image), patch=patch, min_keypoints=3,
+                            samples=samples)
+    torch.cuda.synchronize()
+    exp = PG.patch_grid_sample(cam, kp, kd, image, None, P=patch, min_kp=3, s=samples, opacity=0.5, scale_factor=0.5)
+    _compare(None, res, exp, n_kp)
