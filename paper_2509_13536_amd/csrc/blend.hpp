@@ -101,39 +101,56 @@ __global__ __launch_bounds__(256) void k_bin_place(const uint2 *range, int64_t n
 // lists' lengths kept in registers).  3225 bins of one 1200x680 view: 4.7 us
 // against 4.7 + 4.7 us, and 300 bins 2.3 us against 2.2 + 3.4; four bins a thread
 // is as far as the registers were taken, beyond that the two launches stay.
+// With `totals` (the bins' counts and, at [n], that of the unused slots) it writes
+// the ranges too, of bin n as well.
 constexpr int64_t kBinOrderOneBlock = 4096;
-__global__ __launch_bounds__(1024) void k_bin_order(const uint2 *range, int n, uint32_t *order) {
+__global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint2 *range, int n, uint32_t *order) {
     __shared__ uint32_t h[kOrderClasses];
-    __shared__ uint32_t sums[4];
+    __shared__ uint32_t sums[16];
     constexpr int kPer = (int)(kBinOrderOneBlock / 1024);
+    const int wave = (int)threadIdx.x >> 6, i0 = kPer * (int)threadIdx.x;
     if (threadIdx.x < kOrderClasses) h[threadIdx.x] = 0;
-    __syncthreads();
-    uint2 r[kPer];
+    uint32_t len[kPer];
+    if (totals) {
+        uint32_t sum = 0;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int i = (int)threadIdx.x + 1024 * k;
-        r[k] = i < n ? range[i] : make_uint2(0u, 0u);
+        for (int k = 0; k < kPer; ++k) sum += len[k] = i0 + k <= n ? totals[i0 + k] : 0u;
+        const uint32_t incl = wave_incl_scan_u32(sum);
+        if (lane_id() == 63) sums[wave] = incl;
+        __syncthreads();
+        uint32_t at = incl - sum;
+        for (int w = 0; w < 16; ++w) at += w < wave ? sums[w] : 0u;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (i0 + k <= n) range[i0 + k] = make_uint2(at, at + len[k]);
+            at += len[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const uint2 r = i0 + k < n ? range[i0 + k] : make_uint2(0u, 0u);
+            len[k] = r.y - r.x;
+        }
     }
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPer; ++k)
-        if ((int)threadIdx.x + 1024 * k < n) atomicAdd(&h[len_class(r[k].y - r[k].x)], 1u);
+        if (i0 + k < n) atomicAdd(&h[len_class(len[k])], 1u);
     __syncthreads();
     // the classes' first slots
     const uint32_t c = threadIdx.x < kOrderClasses ? h[threadIdx.x] : 0u;
     const uint32_t incl = wave_incl_scan_u32(c);
-    if (threadIdx.x < kOrderClasses && lane_id() == 63) sums[threadIdx.x >> 6] = incl;
+    if (threadIdx.x < kOrderClasses && lane_id() == 63) sums[wave] = incl;
     __syncthreads();
     if (threadIdx.x < kOrderClasses) {
         uint32_t before = incl - c;
-        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) before += sums[w];
+        for (int w = 0; w < wave; ++w) before += sums[w];
         h[threadIdx.x] = before;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int i = (int)threadIdx.x + 1024 * k;
-        if (i < n) order[atomicAdd(&h[len_class(r[k].y - r[k].x)], 1u)] = (uint32_t)i;
-    }
+    for (int k = 0; k < kPer; ++k)
+        if (i0 + k < n) order[atomicAdd(&h[len_class(len[k])], 1u)] = (uint32_t)(i0 + k);
 }
 
 // Slot of queue q's next bin in the order (queue q takes slots q, q + 8, ...);

@@ -16,7 +16,8 @@
 //                  packed into 64 bits) per covered list bin, a wave writing
 //                  its ranks' keys together (64 ranks, 16 in calls with few;
 //                  coalesced); gathers the blend inputs into rank order
-//   tile sort      stable keys-only radix sort on the bin id (2 passes), so
+//   tile sort      stable keys-only sort on the bin id (one counting pass with
+//                  the ranges and the order, or 2 radix passes), so
 //                  each bin's list is in rank = depth order
 //   k_tile_ranges  [first, last) of every bin; k_bin_count / k_bin_place
 //                  order the bins longest list first
@@ -44,6 +45,7 @@
 
 #include "blend.hpp"
 #include "api_range.hpp"
+#include "binsort.hpp"
 #include "common.hpp"
 #include "project.hpp"
 #include "radix.hpp"
@@ -1296,6 +1298,32 @@ bool split_blend(int btx, int bty, int64_t n_bins, int64_t below) {
     return n_bins < below;
 }
 
+template <int ROUNDS, int BINS>
+void launch_binsort_as(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask, int bits, uint32_t bins,
+                           int stride, uint32_t *table, uint2 *range, uint32_t *order, hipStream_t s) {
+    const unsigned nb = (unsigned)binsort_blocks(M);
+    k_binsort_hist<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, M, mask, bins, stride, table);
+    k_binsort_columns<<<(unsigned)(stride / 32), 1024, 0, s>>>(table, nb, stride);
+    k_bin_order<<<1, 1024, 0, s>>>(table + (int64_t)nb * stride, range, (int)bins, order);
+    k_binsort_scatter<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, out, M, mask, bits, bins, stride, table, range);
+}
+void launch_binsort(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask, int bits, uint32_t bins, int stride,
+                    uint32_t *table, uint2 *range, uint32_t *order, hipStream_t s) {
+    auto go = [&](auto rounds, auto cap) {
+        launch_binsort_as<decltype(rounds)::value, decltype(cap)::value>(in, out, M, mask, bits, bins, stride, table,
+                                                                         range, order, s);
+    };
+    auto by_rounds = [&](auto cap) {
+        switch (binsort_rounds(M)) {
+            case 2: go(std::integral_constant<int, 2>{}, cap); break;
+            case 8: go(std::integral_constant<int, 8>{}, cap); break;
+            default: go(std::integral_constant<int, 16>{}, cap); break;
+        }
+    };
+    if (stride <= kBinSortFewBins) by_rounds(std::integral_constant<int, kBinSortFewBins>{});
+    else by_rounds(std::integral_constant<int, (int)kBinSortMaxBins>{});
+}
+
 void launch_blend_fwd(bool count, bool split, int btx, int bty, unsigned grid, hipStream_t s, const BlendArgs &ba) {
     if (split) {
         if (count) k_blend_fwd<true, 1, 1, true><<<grid, 64, 0, s>>>(ba);
@@ -1710,8 +1738,19 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     MGS_LAUNCHED();
     // stable tile sort on the bin field.  Wide: the values start as the
     // emission index, so at least one pass.
+    uint32_t *bin_order = at<uint32_t>(ws, L.bin_order);
     int ic = 0;
-    for (int sh = 0; sh < tbits && M > 0; sh += 8) {
+    const bool one_pass = packed && M > 0 && S.B_total < kBinSortMaxBins &&
+                          binsort_words(M, S.B_total) <= (int64_t)((L.iv1 - L.iv0) / 4) + M;
+    uint32_t *table = iv[0];  // and on through iv[1]: packed keys have no values
+    const int bstride = (int)binsort_stride(S.B_total);
+    if (one_pass) {
+        const uint32_t mask = (uint32_t)((1ull << tbits) - 1);
+        launch_binsort(it[0], it[1], M, mask, bits_for(S.B_total + 1), (uint32_t)S.B_total, bstride, table, range,
+                       bin_order, s);
+        ic = 1;
+    }
+    for (int sh = 0; sh < tbits && M > 0 && !one_pass; sh += 8) {
         if (packed)
             MGS_HIP(radix_pass_keys<uint64_t>(it[ic], it[ic ^ 1], M, BinDigit{sh, std::min(8, tbits - sh)}, hist, s));
         else
@@ -1725,15 +1764,14 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     info->inst_rank_bits = ea.rank_bits;
     if (Pv == 0)  // else cleared by the emission
         k_fill_u32<<<grid_of(ea.n_zero, 256), 256, 0, s>>>(ea.zero, ea.n_zero, 0u);
-    if (M > 0)
+    if (M > 0 && !one_pass)
         k_tile_ranges<<<grid_of(M, 256), 256, 0, s>>>(reinterpret_cast<const uint32_t *>(it[ic]) + (packed ? 0 : 1),
                                                        packed ? (uint32_t)((1ull << tbits) - 1) : 0xFFFFFFFFu, M,
                                                        S.B_total, range);
-    uint32_t *bin_order = at<uint32_t>(ws, L.bin_order);
-    if (S.B_total > 0) {
+    if (S.B_total > 0 && !one_pass) {
         uint32_t *book = reinterpret_cast<uint32_t *>(range + S.B_total);
         if (S.B_total <= kBinOrderOneBlock) {
-            k_bin_order<<<1, 1024, 0, s>>>(range, (int)S.B_total, bin_order);
+            k_bin_order<<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order);
         } else {
             k_bin_count<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book);
             k_bin_place<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book, bin_order);

@@ -568,3 +568,18 @@ def test_split_forward_with_either_backward(W, H, monkeypatch):
         out.append((st.rgb, st.depth, st.T, d_pose, *[grads[0][k] for k in ("means", "scales", "quats", "opac", "sh")]))
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n,W,H,scale", [(3, 16, 16, -3.0), (900, 64, 48, -2.5), (40_000, 720, 720, -3.6),
+                                         (40_000, 720, 736, -3.6), (150_000, 320, 240, -3.2), (2500, 1008, 1040, -2.5)])
+def test_bin_sort_variants(n, W, H, scale):
+    """The one-pass bin sort at its edges: one bin; 2025 and 2070 bins (half and
+    whole LDS); 2, 8 and 16 rounds a wave (under 2^17, 2^20 and more instances);
+    4095 bins.  Every bin's list is the oracle's, and the image."""
+    sc = synth.tiny_scene(n, W, H, 67, log_scale_mu=scale)
+    print(f"case {n} Gaussians, {W}x{H}", flush=True)
+    st = run_forward(sc)
+    print(f"{int(st.info.n_instances)} instances, {((W + 15) // 16) * ((H + 15) // 16)} bins", flush=True)
+    assert_keys_and_lists(sc, sc.cams[0], st)
+    if n < 100_000:
+        image_parity(sc, sc.cams[0], st)
