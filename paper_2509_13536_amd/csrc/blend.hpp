@@ -1032,20 +1032,43 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
 // taking quadrant w (one pixel per lane), so four times the waves walk the
 // lists.  Wave 0 stages each batch for all four (the masks of all four
 // quadrants); each wave then visits the staged Gaussians live in its quadrant
-// and folds and flushes its sums as the one-wave kernel does, into a per-wave
-// slot of the staged Gaussian's record in LDS; after a block barrier the 256
-// threads add the four waves' values in wave order and write the records.
-// Deterministic; the sums are grouped differently from the one-wave kernel's.
+// and sums their values over its pixels, into a per-wave slot of the staged
+// Gaussian's record in LDS; after a block barrier the 256 threads add the four
+// waves' values in wave order and write the records.  Deterministic; the sums
+// are grouped differently from the one-wave kernel's.
+// With one pixel a lane, all ten values of a visit are products of two, gp and
+// alpha T, with the pixel's offset and its upstream gradient.  So a visit leaves
+// just these two in LDS, and after kDefer visits the wave forms all sums at once:
+// lane 8 f + r takes row r of visit f's quadrant, eight pixels, whose gradients it
+// keeps in registers, and three DPP steps add the rows.  A wave here is bound by
+// the number of its instructions (one alone issues one in seven cycles, and the
+// longest lists set the time): 16 a visit and two LDS accesses in place of 45
+// with the ten values folded by swaps.
+constexpr int kDefer = 8, kPartRow = 72;
 struct StagedBwdSplit {
     StagedG g[64];
-    uint32_t e[64];
-    float part[4][kFold][3][64];  // each wave's folded visits awaiting its flush
+    // (gp, alpha T) of each wave's visits awaiting their sums, by pixel; eight
+    // more a row, so that a flush's reads spread over the banks
+    float2 part[4][kDefer][kPartRow];
     float rec[64][4][kRecord];    // each wave's record values per staged Gaussian
+    uint32_t e[64];
     uint64_t folded[4];           // staged Gaussians each wave wrote
     int64_t item;                 // the bin (block broadcast)
     uint32_t ncq[4];              // each quadrant's largest last-contributor position
     int nlive;
 };
+static_assert(sizeof(StagedBwdSplit) <= 40960, "four blocks on a CU");
+
+// sum over eight neighbouring lanes, in each of them
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum_of_8(float x) {
+    x = dpp_add<0xB1>(x);     // lane ^ 1
+    x = dpp_add<0x4E>(x);     // lane ^ 2
+    return dpp_add<0x141>(x); // 7 - lane: the other four
+}
 
 // one thread's grab for a block: the slot of queue q's next bin, -1 when all
 // eight queues are empty
@@ -1067,15 +1090,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 template <bool POSE>
-__global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
+__global__ __launch_bounds__(256, 4) void k_blend_bwd_split(BlendBwdArgs a) {
     using G = BinGeo<1, 1, true>;
     constexpr int QX = 2;  // quadrant columns of the bin (staging)
     __shared__ StagedBwdSplit sh;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int ff = lane / kRecord, fv = lane - ff * kRecord;
-    const bool flush_lane = ff < kFold;
-    const int src = flush_lane ? fold_src<POSE>(ff, fv) : -1;
-    const int part_off = src >= 0 ? src : 0;
+    const int fvisit = lane >> 3, fk = lane & 7;  // this lane's share of a flush
     int q = blockIdx.x & 7, tries = 0;  // thread 0's queue state
     for (;;) {
         if (threadIdx.x == 0) {
@@ -1109,6 +1129,23 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
             }
             nSg = -(a.bg0 * g0 + a.bg1 * g1 + a.bg2 * g2 + a.bgd * gd);
         }
+        // the upstream gradients of this lane's pixels in a flush, 2 fk + (i & 1) + 16 (i >> 1)
+        float rg0[8], rg1[8], rg2[8], rgd[8];
+        {
+            float4 *gr = reinterpret_cast<float4 *>(&sh.part[w][0][0]);
+            gr[lane] = make_float4(g0, g1, g2, gd);
+            wave_lds_sync();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 gc = gr[2 * fk + (i & 1) + 16 * (i >> 1)];
+                rg0[i] = gc.x;
+                rg1[i] = gc.y;
+                rg2[i] = gc.z;
+                rgd[i] = gc.w;
+            }
+            wave_lds_sync();
+        }
+        const float fx0 = t.qx0[0] + (float)((2 * fk) & 7), fy0 = t.qy0[0] + (float)(fk >> 2);
         const uint32_t ncq = uniform_u32(wave_max_u32(nc));
         if (lane == 0) sh.ncq[w] = ncq;
         __syncthreads();
@@ -1153,19 +1190,66 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
             }
             __syncthreads();
             const int nlive = sh.nlive;
-            uint64_t pend = 0;
-            int nfold = 0;
-            auto flush = [&](int nf) {
-                wave_lds_sync();  // this wave's folded rows are in LDS
-                if (ff < nf) {
-                    const float4 *p = reinterpret_cast<const float4 *>(&sh.part[w][0][0][0] + part_off);
-                    const float4 p0 = p[0], p1 = p[1], p2 = p[2], p3 = p[3];
-                    float r = ((p0.x + p0.y) + (p0.z + p0.w)) + ((p1.x + p1.y) + (p1.z + p1.w)) +
-                              (((p2.x + p2.y) + (p2.z + p2.w)) + ((p3.x + p3.y) + (p3.z + p3.w)));
-                    if (POSE && src < 0) r = 0.0f;
-                    const uint32_t js = (uint32_t)(pend >> (6 * ff)) & 63u;
-                    sh.rec[js][w][fv] = r;
+            // done: the staged Gaussians visited since the last flush, a bit each; the
+            // f-th of them goes to lane f, and from there to the lanes of visit f
+            auto flush = [&](uint64_t done) {
+                wave_lds_sync();  // this wave's values are in LDS
+                const int nf = __popcll(done);
+                const bool mine = (done >> lane) & 1ull;
+                const int f = mine ? __popcll(done & ((1ull << lane) - 1ull)) : 63;
+                const int js = __builtin_amdgcn_ds_bpermute(4 * fvisit, __builtin_amdgcn_ds_permute(4 * f, lane));
+                const float2 c = sh.g[js].xy;
+                const float4 *pairs = reinterpret_cast<const float4 *>(&sh.part[w][fvisit][2 * fk]);
+                const float dx0 = c.x - fx0, dx1 = c.x - (fx0 + 1.0f);
+                // (gp, alpha T) of the pixels, [block of 16][of the two]
+                float gp[4][2], wk[4][2];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const float4 two = pairs[8 * m];
+                    gp[m][0] = two.x;
+                    wk[m][0] = two.y;
+                    gp[m][1] = two.z;
+                    wk[m][1] = two.w;
                 }
+                // one value at a time (its eight terms are few registers)
+                auto total = [&](auto term) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    float x[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const float x0 = term(0, u) + term(2, u);
+                        x[u] = x0 + (term(1, u) + term(3, u));
+                    }
+                    return sum_of_8(x[0] + x[1]);
+                };
+                float vs[kRecord] = {};
+                const float dx[2] = {dx0, dx1};
+                float dy[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) dy[m] = c.y - (fy0 + (float)(2 * m));
+                if (!POSE) {
+                    vs[0] = total([&](int m, int u) { return gp[m][u]; });
+                    vs[6] = total([&](int m, int u) { return wk[m][u] * rg0[2 * m + u]; });
+                    vs[7] = total([&](int m, int u) { return wk[m][u] * rg1[2 * m + u]; });
+                    vs[8] = total([&](int m, int u) { return wk[m][u] * rg2[2 * m + u]; });
+                }
+                vs[9] = total([&](int m, int u) { return wk[m][u] * rgd[2 * m + u]; });
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    for (int u = 0; u < 2; ++u) {
+                        wk[m][u] = gp[m][u] * dx[u];  // from here on gp dx
+                        gp[m][u] = gp[m][u] * dy[m];  // and gp dy
+                    }
+                vs[1] = total([&](int m, int u) { return wk[m][u]; });
+                vs[3] = total([&](int m, int u) { return wk[m][u] * dx[u]; });
+                vs[4] = total([&](int m, int u) { return wk[m][u] * dy[m]; });
+                vs[2] = total([&](int m, int u) { return gp[m][u]; });
+                vs[5] = total([&](int m, int u) { return gp[m][u] * dy[m]; });
+                // lane fk < 5 writes values 2 fk and 2 fk + 1
+                float2 o = make_float2(vs[0], vs[1]);
+#pragma unroll
+                for (int i = 1; i < 5; ++i) o = fk == i ? make_float2(vs[2 * i], vs[2 * i + 1]) : o;
+                if (fvisit < nf && fk < 5) *reinterpret_cast<float2 *>(&sh.rec[js][w][2 * fk]) = o;
                 wave_lds_sync();  // sh.part[w] may be written again
             };
             // the staged Gaussians this wave visits: live in its quadrant and
@@ -1180,19 +1264,23 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
             }
             const uint64_t visited = ballot(mine);
             const bool batch_clamp = ballot(mine && slot_clamp) != 0ull;
-            auto visits = [&](auto clamp_v) {
+            uint64_t left = visited;
+            auto visits = [&](auto clamp_v) {  // the next kDefer of them
             constexpr bool CLAMP = decltype(clamp_v)::value;
-            for (uint64_t left = visited; left; left &= left - 1ull) {
+            float2 *to = &sh.part[w][0][lane];
+            int n = 0;
+            do {
                 const int j = __ffsll((long long)left) - 1;
+                left &= ~(1ull << j);
                 const StagedG &sj = sh.g[j];
-                const float2 g = sj.xy;
                 const float4 cn4 = sj.cn;
                 const float4 cd4 = sj.cd;
-                const uint32_t pos = __builtin_amdgcn_readlane(slot_pos, j);
-                const float dx = g.x - t.fpx[0];
+                const float4 xp = *reinterpret_cast<const float4 *>(&sj.xy);  // xy, pos
+                const uint32_t pos = __float_as_uint(xp.z);
+                const float dx = xp.x - t.fpx[0];
                 float adx2, bdx;
                 shared_dx(cn4.x, cn4.y, cn4.w, dx, adx2, bdx);
-                const float dy = g.y - t.fpy[0];
+                const float dy = xp.y - t.fpy[0];
                 const AlphaEval ev = CLAMP ? alpha_at(adx2, bdx, cn4.z, dy) : alpha_at_unclamped(adx2, bdx, cn4.z, dy);
                 const bool ok = (pos < nc) && (ev.alpha >= kAlphaMin);
                 const float al = ok ? ev.alpha : 0.0f;
@@ -1201,34 +1289,18 @@ __global__ __launch_bounds__(256) void k_blend_bwd_split(BlendBwdArgs a) {
                                                 __builtin_fmaf(cd4.y, g1, __builtin_fmaf(cd4.x, g0, nSg))));
                 const float wk = al * Ti;
                 const float gp = (!CLAMP || ev.aun <= kAlphaMax) ? wk * dd : 0.0f;
-                const float gx = gp * dx, gy = gp * dy;
                 nSg = __builtin_fmaf(-al, dd, nSg);
                 Tc = Ti;
-                if constexpr (POSE) {
-                    const float vals[6] = {gx, gy, gx * dx, gx * dy, gy * dy, wk * gd};
-                    float z[2];
-                    wave_fold_pose(vals, z);
-                    sh.part[w][nfold][0][lane] = z[0];
-                    sh.part[w][nfold][1][lane] = z[1];
-                } else {
-                    const float vals[kRecord] = {gp, gx, gy, gx * dx, gx * dy, gy * dy, wk * g0, wk * g1, wk * g2, wk * gd};
-                    float z[3];
-                    wave_fold_record(vals, z);
-                    sh.part[w][nfold][0][lane] = z[0];
-                    sh.part[w][nfold][1][lane] = z[1];
-                    sh.part[w][nfold][2][lane] = z[2];
-                }
-                pend |= (uint64_t)j << (6 * nfold);
-                if (++nfold == kFold) {
-                    flush(kFold);
-                    nfold = 0;
-                    pend = 0;
-                }
-            }
+                *to = make_float2(gp, wk);
+                to += kPartRow;
+            } while (++n < kDefer && left);
             };
-            if (batch_clamp) visits(std::true_type{});
-            else visits(std::false_type{});
-            if (nfold) flush(nfold);
+            while (left) {
+                const uint64_t before = left;
+                if (batch_clamp) visits(std::true_type{});
+                else visits(std::false_type{});
+                flush(before ^ left);
+            }
             if (lane == 0) sh.folded[w] = visited;
             __syncthreads();
             // records: the four waves' values in wave order, for the staged

@@ -1879,9 +1879,9 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     bool pose_blend = pose_only;
     for (int m = 0; m < n_maps; ++m)
         if (S.maps[m].sh_degree != 0) pose_blend = false;
-    // few bins: four-wave blocks, one per bin, five to a CU (their LDS)
+    // few bins: four-wave blocks, one per bin, four to a CU (their registers)
     const bool split = split_blend(S.btx, S.bty, S.B_total, kSplitBwdBelowBins);
-    const int64_t grid = split ? std::max<int64_t>(1, std::min<int64_t>(S.B_total, (int64_t)num_cus() * 5))
+    const int64_t grid = split ? std::max<int64_t>(1, std::min<int64_t>(S.B_total, (int64_t)num_cus() * 4))
                                : blend_grid(S.B_total);
     launch_blend_bwd(split, S.btx, S.bty, (unsigned)grid, s, bb, pose_blend);
     MGS_LAUNCHED();

@@ -583,3 +583,25 @@ def test_bin_sort_variants(n, W, H, scale):
     assert_keys_and_lists(sc, sc.cams[0], st)
     if n < 100_000:
         image_parity(sc, sc.cams[0], st)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 17, 63, 65, 130])
+def test_split_backward_deferred_sums(n):
+    """The split backward forms its sums after every eight visits and at the end
+    of a batch of 64: one tile whose quadrants are visited by about n Gaussians,
+    against the oracle."""
+    sc = synth.tiny_scene(n, 16, 16, 71 + n, sh_degree=0, pose=True, log_scale_mu=-1.5, opac_max=0.3)
+    cam = sc.cams[0]
+    print(f"case {n} Gaussians on a tile", flush=True)
+    st = run_forward(sc, need_backward=True)
+    amb = oracle.forward(sc, cam)["amb"]
+    g_rgb, g_d = synth.upstream_grads([cam], n)
+    g_rgb, g_d = g_rgb[0], g_d[0]
+    g_rgb[:, amb] = 0
+    g_d[amb] = 0
+    grads, d_pose = render_backward(st, torch.from_numpy(g_rgb.reshape(-1)).cuda(),
+                                    torch.from_numpy(g_d.reshape(-1)).cuda())
+    gref = oracle.backward(sc, cam, g_rgb, g_d)
+    for name in ("means", "scales", "quats", "opac", "sh"):
+        grad_parity(grads[0][name].cpu().numpy(), gref[name], name)
+    grad_parity(d_pose.cpu().numpy()[0], gref["pose"], "pose")
