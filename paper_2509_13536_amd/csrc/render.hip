@@ -8,7 +8,8 @@
 //   k_sum_blocks   the totals, written to a pinned host mailbox: the host waits
 //                  for this one read-back (the layout of the rest depends on it)
 //   k_compact_pairs  (depth key, pair) of the visible pairs, in pair order
-//   pair sort      stable radix sort on (view, depth key - its minimum)
+//   pair sort      stable sort on (view, depth key - its minimum): radix, or
+//                  k_rank_pairs for one view with few pairs
 //                  => depth rank of each visible pair (ties by index); the
 //                  last pass writes each rank's tile count
 //   rank scan      scan of tile counts in rank order => instance offsets
@@ -19,7 +20,8 @@
 //   tile sort      stable keys-only sort on the bin id (one counting pass with
 //                  the ranges and the order, or 2 radix passes), so
 //                  each bin's list is in rank = depth order
-//   k_tile_ranges  [first, last) of every bin; k_bin_count / k_bin_place
+//   k_tile_ranges  [first, last) of every bin (after the radix passes);
+//                  k_bin_order, or for many bins k_bin_count / k_bin_place,
 //                  order the bins longest list first
 //   k_blend_fwd    persistent, one wave per list bin: a 16x16 tile (4 pixels
 //                  per lane), or 2x1 tiles (8 per lane) in calls with many
