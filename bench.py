@@ -251,11 +251,10 @@ def configs_bench(only=""):
     print(json.dumps({"configs": out}), flush=True)
 
 
-# Algorithmic HBM bytes of the mapping loss per pixel: per colour channel the
-# first pass reads both images (8 B) and writes three derivative maps (12 B),
-# the second reads the maps and both images (20 B) and writes the gradient
-# (4 B); the depth term reads two depths and writes one gradient (12 B).
-LOSS_BYTES_PER_PIXEL = 3 * (8 + 12 + 20 + 4) + 12
+# Algorithmic HBM bytes of the mapping loss per pixel: per colour channel both
+# images are read (8 B) and the gradient is written (4 B); the depth term reads
+# two depths and writes one gradient (12 B).
+LOSS_BYTES_PER_PIXEL = 3 * (8 + 4) + 12
 # Algorithmic VALU lane-operations of the loss per pixel and colour channel (the
 # SSIM stencil dominates; a reciprocal counts 4): first pass 3 products, 5 moments
 # x 11 taps along rows and again along columns (110), SSIM with its three
