@@ -22,21 +22,23 @@
 namespace mgs {
 
 constexpr int kBinSortThreads = 512, kBinSortWaves = kBinSortThreads / 64;
-// With the bin of unused slots: 64 KB of 16-bit counters and 16 KB of bases, two
-// blocks on a CU.  With twice the bins one block would be left there, and the
-// single pass is bound by its latency; those calls keep the radix passes.
-constexpr int64_t kBinSortMaxBins = 4096;
+// With the bin of unused slots: 128 KB of 16-bit counters, one block on a CU, whose
+// bases no longer fit beside them and are gathered (1.1M instances over 4270 bins:
+// 42 us for the four launches against 57 for the radix passes, ranges and order).
+// Up to kBinSortMidBins they are 64 KB and 16 KB of bases, two blocks on a CU, up
+// to kBinSortFewBins half of that.
+constexpr int64_t kBinSortMaxBins = 8192;
 
-constexpr int kBinSortFewBins = 2048;  // half the LDS, twice the blocks on a CU
-constexpr int kBinSortBits = 12;
+constexpr int kBinSortFewBins = 2048, kBinSortMidBins = 4096;
+constexpr int kBinSortBits = 13;
 static_assert(kBinSortMaxBins == int64_t(1) << kBinSortBits, "a bin's bits");
 
 // Rounds of 64 instances a wave takes: many where the table of counts (a row a
 // block) has to stay small against the instances, few where the blocks have to
 // fill the chip.  All launches together at 2 / 4 / 8 / 16 rounds, us: 96k
 // instances over 1131 bins 12.6 / 13.1 / 16.2 / 22, 5.3M over 1200 89 / 66 / 58 /
-// 61, 6.9M over 3225 - / 104 / 79 / 79.
-inline int binsort_rounds(int64_t m) { return m < (int64_t(1) << 17) ? 2 : m < (int64_t(1) << 20) ? 8 : 16; }
+// 61, 6.9M over 3225 - / 104 / 79 / 79; 1.1M at 16 rounds would be 139 blocks.
+inline int binsort_rounds(int64_t m) { return m < (int64_t(1) << 17) ? 2 : m < (int64_t(1) << 22) ? 8 : 16; }
 inline int64_t binsort_blocks(int64_t m) { return ceil_div(m, kBinSortThreads * binsort_rounds(m)); }
 inline int64_t binsort_stride(int64_t bins) { return (bins + 1 + 63) / 64 * 64; }
 // words of the table of counts, with the row of totals after it
@@ -114,7 +116,8 @@ __global__ __launch_bounds__(kBinSortThreads) void k_binsort_scatter(const uint6
                                                                      int stride, const uint32_t *table,
                                                                      const uint2 *range) {
     __shared__ uint32_t cnt32[kBinSortWaves][BINS / 2];  // two 16-bit counters a word
-    __shared__ uint32_t gbase[BINS];
+    constexpr bool kBases = BINS <= kBinSortMidBins;  // the bases in LDS, else gathered
+    __shared__ uint32_t gbase[kBases ? BINS : 1];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int64_t part = binsort_part(blockIdx.x, gridDim.x);
     const int64_t base = part * (kBinSortThreads * ROUNDS) + wave * (64 * ROUNDS) + lane;
@@ -158,6 +161,7 @@ __global__ __launch_bounds__(kBinSortThreads) void k_binsort_scatter(const uint6
             cnt32[w][i] = ex;
             ex += c;  // both halves: a block holds fewer than 2^16 instances
         }
+        if (!kBases) continue;
         const uint2 t = *reinterpret_cast<const uint2 *>(table + part * stride + 2 * i);
         gbase[2 * i] = 2 * i <= (int)n_bins ? range[2 * i].x + t.x : 0u;
         gbase[2 * i + 1] = 2 * i + 1 <= (int)n_bins ? range[2 * i + 1].x + t.y : 0u;
@@ -167,7 +171,8 @@ __global__ __launch_bounds__(kBinSortThreads) void k_binsort_scatter(const uint6
     for (int r = 0; r < ROUNDS; ++r) {
         if (base + 64 * r >= m) continue;
         const uint32_t d = binsort_bin((uint32_t)key[r], mask, n_bins);
-        out[gbase[d] + cnt[d] + rank[r]] = key[r];
+        const uint32_t at = kBases ? gbase[d] : range[d].x + table[part * stride + d];
+        out[at + cnt[d] + rank[r]] = key[r];
     }
 }
 

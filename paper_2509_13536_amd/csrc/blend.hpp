@@ -97,17 +97,17 @@ __global__ __launch_bounds__(256) void k_bin_place(const uint2 *range, int64_t n
     }
 }
 
-// Both in one launch of one block, for calls with few bins (four a thread, their
+// Both in one launch of one block, for calls with few bins (kPer a thread, their
 // lists' lengths kept in registers).  3225 bins of one 1200x680 view: 4.7 us
-// against 4.7 + 4.7 us, and 300 bins 2.3 us against 2.2 + 3.4; four bins a thread
-// is as far as the registers were taken, beyond that the two launches stay.
+// against 4.7 + 4.7 us, and 300 bins 2.3 us against 2.2 + 3.4; with eight a thread
+// (4270 bins) 8.0 us, no less than the two launches, which stay beyond 4096.
 // With `totals` (the bins' counts and, at [n], that of the unused slots) it writes
 // the ranges too, of bin n as well.
 constexpr int64_t kBinOrderOneBlock = 4096;
+template <int kPer>
 __global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint2 *range, int n, uint32_t *order) {
     __shared__ uint32_t h[kOrderClasses];
     __shared__ uint32_t sums[16];
-    constexpr int kPer = (int)(kBinOrderOneBlock / 1024);
     const int wave = (int)threadIdx.x >> 6, i0 = kPer * (int)threadIdx.x;
     if (threadIdx.x < kOrderClasses) h[threadIdx.x] = 0;
     uint32_t len[kPer];

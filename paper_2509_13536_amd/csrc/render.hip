@@ -1306,7 +1306,7 @@ void launch_binsort_as(const uint64_t *in, uint64_t *out, int64_t M, uint32_t ma
     const unsigned nb = (unsigned)binsort_blocks(M);
     k_binsort_hist<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, M, mask, bins, stride, table);
     k_binsort_columns<<<(unsigned)(stride / 32), 1024, 0, s>>>(table, nb, stride);
-    k_bin_order<<<1, 1024, 0, s>>>(table + (int64_t)nb * stride, range, (int)bins, order);
+    k_bin_order<(BINS > kBinSortMidBins ? 8 : 4)><<<1, 1024, 0, s>>>(table + (int64_t)nb * stride, range, (int)bins, order);
     k_binsort_scatter<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, out, M, mask, bits, bins, stride, table, range);
 }
 void launch_binsort(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask, int bits, uint32_t bins, int stride,
@@ -1323,6 +1323,7 @@ void launch_binsort(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask,
         }
     };
     if (stride <= kBinSortFewBins) by_rounds(std::integral_constant<int, kBinSortFewBins>{});
+    else if (stride <= kBinSortMidBins) by_rounds(std::integral_constant<int, kBinSortMidBins>{});
     else by_rounds(std::integral_constant<int, (int)kBinSortMaxBins>{});
 }
 
@@ -1773,7 +1774,7 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     if (S.B_total > 0 && !one_pass) {
         uint32_t *book = reinterpret_cast<uint32_t *>(range + S.B_total);
         if (S.B_total <= kBinOrderOneBlock) {
-            k_bin_order<<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order);
+            k_bin_order<4><<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order);
         } else {
             k_bin_count<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book);
             k_bin_place<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book, bin_order);

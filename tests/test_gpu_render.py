@@ -605,3 +605,14 @@ def test_split_backward_deferred_sums(n):
     for name in ("means", "scales", "quats", "opac", "sh"):
         grad_parity(grads[0][name].cpu().numpy(), gref[name], name)
     grad_parity(d_pose.cpu().numpy()[0], gref["pose"], "pose")
+
+
+@pytest.mark.parametrize("n,W,H", [(20_000, 1024, 1008), (20_000, 1024, 1024), (9000, 1456, 1440), (9000, 1456, 1456)])
+def test_bin_sort_of_many_bins(n, W, H):
+    """4032 and 4096 bins, either side of the one-pass sort's half LDS, and 8190
+    and 8281, the last of its range and the first that takes radix passes."""
+    sc = synth.tiny_scene(n, W, H, 73, log_scale_mu=-2.6)
+    print(f"case {W}x{H}", flush=True)
+    st = run_forward(sc)
+    assert_keys_and_lists(sc, sc.cams[0], st)
+    image_parity(sc, sc.cams[0], st)
