@@ -340,6 +340,9 @@ typedef struct mgs_loss_opts {
  * dL_drgb     device float packed like rgb, written
  * dL_ddepth   device float packed like depth, written (required with depth)
  * dL_dscales  device float [n_gauss][3], written (required with scales)
+ *             A gradient may take its input's place: dL_drgb that of rgb or gt_rgb
+ *             (or memory that overlaps them, at the price of a copy), dL_ddepth
+ *             that of depth or gt_depth, dL_dscales that of scales.
  * ws, ws_bytes, ws_required (host): workspace; *ws_required is set on return in
  *             every case; MGS_ERR_WORKSPACE when ws_bytes is smaller (nothing
  *             launched).  About 36 bytes per pixel.

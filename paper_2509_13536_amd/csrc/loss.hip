@@ -6,10 +6,12 @@
 //                 over the images.  Blocks of the depth residual and its
 //                 gradient.  Blocks of L_iso, in fp64, so that the sign of each
 //                 scale's deviation from the mean scale is decided exactly.
+//   k_loss_put    only where the colour gradient overlaps an image: copies it there
 //   k_loss_final  one block: fixed-order fp64 sums of the blocks' partial sums,
 //                 then the total in view order, so the values are deterministic.
 //
 // The colour terms move 8 bytes in and 4 out per pixel and channel.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -472,6 +474,12 @@ __global__ __launch_bounds__(256, 5) void k_loss(SsimArgs a, RestArgs r) {
     }
 }
 
+// The colour gradient of a call whose dL_drgb overlaps an image.  A tile reads its
+// neighbours' pixels, so k_loss leaves the gradient in the workspace there.
+__global__ __launch_bounds__(256) void k_loss_put(const float *from, float *to, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) to[i] = from[i];
+}
+
 // ---------------------------------------------------------------- values
 struct FinalArgs {
     ViewTable views;
@@ -604,6 +612,12 @@ int ssim_chunks(const int32_t *sizes, int32_t n_views) {
     return best;
 }
 
+bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
+    if (!a || !b) return false;
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + 4 * (uintptr_t)nb && q < p + 4 * (uintptr_t)na;
+}
+
 // The loss after the argument checks.  views: host room for n_views entries.
 // ws == nullptr with ws_bytes == 0 only sizes the call (*ws_required).
 mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, const float *gt_rgb,
@@ -662,6 +676,14 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
         }
     }
     float *partial = at<float>(ws, off_part), *depth_partial = partial + 6 * tiles;
+    // Outputs over the images, which k_loss reads while it writes: the colour
+    // gradient is formed behind the partial sums (24 bytes a tile of at least one
+    // pixel and 4 a depth block leave the 12 a pixel), L_iso has a launch of its own.
+    const auto over_images = [&](const float *out, int64_t n) {
+        return overlap(out, n, rgb, 3 * P) || overlap(out, n, gt_rgb, 3 * P) || overlap(out, n, depth, P) ||
+               overlap(out, n, gt_depth, P);
+    };
+    const bool put = over_images(dL_drgb, 3 * P), iso_after = iso && over_images(dL_dscales, 3 * n_gauss);
     SsimArgs a;
     a.views = vt;
     a.n_tiles = tiles;
@@ -669,7 +691,7 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
     a.rgb = rgb;
     a.gt = gt_rgb;
     a.partial = partial;
-    a.d_rgb = dL_drgb;
+    a.d_rgb = put ? depth_partial + n_depth : dL_drgb;
     a.lam = opts->lambda_ssim;
     {
         double w[kLW], sum = 0.0;
@@ -693,8 +715,17 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
     r.w_iso = opts->w_iso;
     r.d_scales = dL_dscales;
     r.iso_partial = iso_part;
-    k_loss<<<(unsigned)(8 * ceil_div(3 * tiles, 8) + n_depth + n_iso), 256, 0, s>>>(a, r);
+    k_loss<<<(unsigned)(8 * ceil_div(3 * tiles, 8) + n_depth + (iso_after ? 0 : n_iso)), 256, 0, s>>>(a, r);
     MGS_LAUNCHED();
+    if (put) {
+        k_loss_put<<<(unsigned)std::min<int64_t>(ceil_div(3 * P, 1024), 4096), 256, 0, s>>>(a.d_rgb, dL_drgb, 3 * P);
+        MGS_LAUNCHED();
+    }
+    if (iso_after) {
+        a.n_tiles = r.n_depth = 0;
+        k_loss<<<(unsigned)n_iso, 256, 0, s>>>(a, r);
+        MGS_LAUNCHED();
+    }
     FinalArgs f;
     f.views = vt;
     f.n_tiles = tiles;

@@ -12,7 +12,8 @@ import torch
 import synth
 from oracle import loss as OL
 from paper_2509_13536_amd import autograd as AG
-from paper_2509_13536_amd import GaussianMap, View, mapping_loss, render_backward, render_forward
+from paper_2509_13536_amd import (GaussianMap, LossResult, View, mapping_loss, mapping_loss_noalloc, render_backward,
+                                  render_forward)
 
 from gpu_helpers import grad_parity
 
@@ -159,3 +160,36 @@ def test_loss_autograd_feeds_the_renderer():
     assert torch.equal(means.grad, grads[0]["means"])
     assert torch.equal(opac.grad, grads[0]["opac"])
     assert torch.equal(scales.grad, grads[0]["scales"] + res.d_scales)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("place", ["rgb", "gt", "shifted", "depth", "scales", "scales_on_rgb"])
+def test_gradient_in_its_inputs_place(place, noalloc):
+    """A gradient written over an image that neighbouring tiles still read: the
+    bits of the call with arrays of their own.  Three strips of columns and several
+    segments of rows a view, so that tiles meet on every side."""
+    sizes = [(163, 105), (120, 90)]
+    rng = np.random.default_rng(17)
+    rgb, gt, d, gd = (_flat(x) for x in _images(rng, sizes))
+    scales = torch.from_numpy(rng.uniform(0.01, 0.1, size=(1025, 3)).astype(np.float32)).cuda()
+    run = mapping_loss_noalloc if noalloc else mapping_loss
+    print("case gradient over", place, noalloc, flush=True)
+    ref = run(sizes, rgb, gt, d, gd, scales, 0.2, 0.7, 3.0)
+    out = LossResult(torch.empty_like(ref.loss), torch.empty_like(rgb), torch.empty_like(d), torch.empty_like(scales))
+    if place == "rgb":
+        out.d_rgb = rgb
+    elif place == "gt":
+        out.d_rgb = gt
+    elif place == "shifted":
+        both = torch.empty(rgb.numel() + 6007, device="cuda")
+        both[:rgb.numel()] = rgb
+        rgb, out.d_rgb = both[:rgb.numel()], both[6007:]
+    elif place == "depth":
+        out.d_depth = d
+    elif place == "scales":
+        out.d_scales = scales
+    else:
+        out.d_scales = rgb[5000:5000 + scales.numel()].view_as(scales)
+    run(sizes, rgb, gt, d, gd, scales, 0.2, 0.7, 3.0, out=out)
+    for k in ("loss", "d_rgb", "d_depth", "d_scales"):
+        assert torch.equal(getattr(ref, k), getattr(out, k)), k
