@@ -32,13 +32,17 @@ constexpr float kC2 = 9e-4f;        // (0.03)^2
 
 struct LossView {
     int32_t W, H;
-    int32_t strips, pad;  // strips of kSC columns
-    int64_t tile_base;    // first SSIM tile of the view (strips of one channel, cut into segments of rows)
-    int64_t pix_base;     // first pixel in the packed one-channel layout
-    int64_t depth_base;   // first block of k_loss_depth
-    float inv_n3;         // 1 / (3 W H)
-    float inv_n1;         // 1 / (W H)
+    int32_t strips;      // strips of kSC columns
+    int32_t tile_base;   // first SSIM tile of the view (strips of one channel, cut into segments of rows)
+    int64_t pix_base;    // first pixel in the packed one-channel layout
+    int32_t depth_base;  // first block of the depth residual
+    float inv_n3;        // 1 / (3 W H)
+    float inv_n1;        // 1 / (W H)
+    int32_t pad;
 };
+// The table of 89 views fits the arguments of k_arg_copy, and its size is a part
+// of the workspace that the entry points ask for.
+static_assert(sizeof(LossView) == 40 && 89 * sizeof(LossView) <= 4 * (size_t)kArgCopyWords, "view table");
 
 // A call of at most kArgViews views carries its view table in the kernel
 // arguments; a larger one copies it to the workspace.
@@ -633,9 +637,9 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
         L.H = H;
         L.strips = (int32_t)ceil_div(W, kSC);
         L.pad = 0;
-        L.tile_base = tiles;
+        L.tile_base = (int32_t)tiles;  // the counts are checked below
         L.pix_base = P;
-        L.depth_base = n_depth;
+        L.depth_base = (int32_t)n_depth;
         L.inv_n3 = (float)(1.0 / (3.0 * (double)W * (double)H));
         L.inv_n1 = (float)(1.0 / ((double)W * (double)H));
         tiles += L.strips * ceil_div(H, 8 * nch - kWarm);
@@ -651,7 +655,8 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
     const size_t off_views = b.take(sizeof(LossView) * (size_t)n_views);
     // The size that the interface states, 36 bytes per pixel and 48 per 32x32
     // square, is what callers plan for; the partial sums take a part of it.
-    const size_t off_part = b.take(4 * (size_t)9 * (size_t)P + 256 + 4 * (size_t)12 * (size_t)squares);
+    const size_t off_part = b.take(4 * (size_t)9 * (size_t)P);
+    b.take(4 * (size_t)12 * (size_t)squares);
     const size_t off_iso = b.take(8 * (size_t)std::max<int64_t>(iso ? ceil_div(n_gauss, 256) : 0, 1));
     const size_t off_terms = b.take(8 * (size_t)(n_views + 1));
     *ws_required = b.size();

@@ -330,3 +330,49 @@ def test_roctx_ranges_when_asked(tmp_path):
         env = dict(os.environ, MGS_ROCTX=flag)
         r = subprocess.run(["python3", "-c", code], capture_output=True, text=True, env=env, timeout=120)
         assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+# ---------------------------------------------------------------- the loss's workspace
+def _loss_required(lib, sizes, n_gauss, noalloc=False):
+    """What a call over these views asks for (ones that launch nothing)."""
+    sz = (C.c_int32 * (2 * len(sizes)))(*[x for wh in sizes for x in wh])
+    o, req, p = _abi.LossOpts(0.2, 1.0, 1.0, 0), C.c_size_t(0), C.c_void_p(FAKE)
+    scales = p if n_gauss else None
+    if noalloc:
+        st = lib.mgs_mapping_loss_noalloc(sz, len(sizes), p, p, p, p, scales, n_gauss, C.byref(o), C.byref(req), p, p,
+                                          p, scales, None)
+    else:
+        st = lib.mgs_mapping_loss(sz, len(sizes), p, p, p, p, scales, n_gauss, C.byref(o), None, 0, C.byref(req), p, p,
+                                  p, scales, None)
+    return st, int(req.value)
+
+
+def _planned(sizes, n_gauss):
+    """40 bytes a view, 36 a pixel, 48 a 32x32 square, 8 for 256 Gaussians, 8 a
+    view and one, each rounded to 256."""
+    P = sum(w * h for w, h in sizes)
+    squares = sum(-(-w // 32) * -(-h // 32) for w, h in sizes)
+    parts = (40 * len(sizes), 36 * P, 48 * squares, 8 * max(-(-n_gauss // 256), 1), 8 * (len(sizes) + 1))
+    return sum(-(-b // 256) * 256 for b in parts)
+
+
+@pytest.mark.parametrize("sizes,n_gauss", [
+    ([(1, 1)], 0), ([(641, 479)], 1), ([(1200, 680)] * 8, 500_000), ([(33, 65), (1, 300), (300, 1)], 257),
+    ([(7, 5)] * 12, 0), ([(16, 16)] * 13, 77), ([(20, 30)] * 89, 0), ([(64, 48)] * 1000, 1024),
+])
+def test_loss_workspace_is_what_callers_planned_for(sizes, n_gauss):
+    st, got = _loss_required(_abi.load(), sizes, n_gauss)
+    assert st == _abi.MGS_ERR_WORKSPACE and got == _planned(sizes, n_gauss)
+
+
+def test_loss_calls_that_just_fit_the_fixed_scratch():
+    """The largest images within 256 bytes of the 64 MiB still fit them, and one
+    row more is refused."""
+    lib, scratch = _abi.load(), 64 << 20
+    fits = [(w, h) for w in range(1, 16385) for h in [min(scratch // (36 * w), 16384)]
+            if scratch - 256 < _planned([(w, h)], 0) <= scratch]
+    assert fits
+    for w, h in fits:
+        assert _loss_required(lib, [(w, h)], 0)[1] <= scratch
+        st, need = _loss_required(lib, [(w, h + 1), (w, h)], 0, noalloc=True)
+        assert need > scratch and st == _abi.MGS_ERR_SCRATCH

@@ -12,8 +12,8 @@ import torch
 import synth
 from oracle import loss as OL
 from paper_2509_13536_amd import autograd as AG
-from paper_2509_13536_amd import (GaussianMap, LossResult, View, mapping_loss, mapping_loss_noalloc, render_backward,
-                                  render_forward)
+from paper_2509_13536_amd import (GaussianMap, LossResult, View, Workspace, mapping_loss, mapping_loss_noalloc,
+                                  render_backward, render_forward)
 
 from gpu_helpers import grad_parity
 
@@ -193,3 +193,27 @@ def test_gradient_in_its_inputs_place(place, noalloc):
     run(sizes, rgb, gt, d, gd, scales, 0.2, 0.7, 3.0, out=out)
     for k in ("loss", "d_rgb", "d_depth", "d_scales"):
         assert torch.equal(getattr(ref, k), getattr(out, k)), k
+
+
+def test_captured_call_of_89_views():
+    """The view table of up to 89 views travels in kernel arguments, so the call
+    can be captured; replays on new images give the eager call's bits."""
+    sizes = [(20 + k % 7, 17 + k % 5) for k in range(89)]
+    rng = np.random.default_rng(18)
+    first, second = (tuple(_flat(x) for x in _images(rng, sizes)) for _ in range(2))
+    print("case captured loss of 89 views", flush=True)
+    args = tuple(x.clone() for x in first)
+    ws = Workspace()
+    eager = [mapping_loss(sizes, *x, lambda_ssim=0.2, w_depth=0.7, ws=ws) for x in (first, second)]
+    out = LossResult(*(torch.empty_like(x) for x in (eager[0].loss, eager[0].d_rgb, eager[0].d_depth)), None)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mapping_loss(sizes, *args, lambda_ssim=0.2, w_depth=0.7, ws=ws, out=out)
+    for x, ref in ((second, eager[1]), (first, eager[0]), (second, eager[1])):
+        for a, b in zip(args, x):
+            a.copy_(b)
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in ("loss", "d_rgb", "d_depth"):
+            assert torch.equal(getattr(ref, k), getattr(out, k)), k
