@@ -7,8 +7,9 @@
 //                 gradient.  Blocks of L_iso, in fp64, so that the sign of each
 //                 scale's deviation from the mean scale is decided exactly.
 //   k_loss_put    only where the colour gradient overlaps an image: copies it there
-//   k_loss_final  one block: fixed-order fp64 sums of the blocks' partial sums,
-//                 then the total in view order, so the values are deterministic.
+//   k_loss_final  one block: fixed-order fp64 sums of the blocks' partial sums (of
+//                 many views k_loss_views before it), then the total in view
+//                 order, so the values are deterministic.
 //
 // The colour terms move 8 bytes in and 4 out per pixel and channel.
 #include <algorithm>
@@ -494,75 +495,97 @@ struct FinalArgs {
     int64_t n_gauss;
     float lam, w_depth, w_iso;
     int has_depth;
-    double *terms;  // [n_views]: L_view of each view
+    double *terms;  // [n_views]: L_view of each view, of more than kArgViews
     float *loss;    // [4 n_views + 2]
 };
 
-// One block of 16 waves: a round takes up to 16 views, with 16 / views waves each;
-// then L_iso over the block and the total in view order.
-__global__ __launch_bounds__(1024) void k_loss_final(FinalArgs a) {
+// Terms of views v0 .. v0 + at_once - 1, by 16 waves, `share` to a view, summed in
+// a fixed order.  out: [at_once] L_view.
+__device__ __forceinline__ void view_terms(const FinalArgs &a, int v0, int at_once, int share, double *out) {
     __shared__ double red[3][16];
-    const int lane = lane_id(), wave = threadIdx.x >> 6, nv = a.views.n;
-    const int at_once = nv < 16 ? nv : 16, share = 16 / at_once;
-    for (int v0 = 0; v0 < nv; v0 += at_once) {
-        const int v = v0 + wave / share;
-        double sS = 0.0, sL = 0.0, sD = 0.0;
-        if (wave < at_once * share && v < nv) {
-            const int64_t t0 = a.views[v].tile_base, t1 = v + 1 < nv ? a.views[v + 1].tile_base : a.n_tiles;
-            const int64_t b0 = a.views[v].depth_base, b1 = v + 1 < nv ? a.views[v + 1].depth_base : a.n_depth;
-            const int64_t first = (wave % share) * 64 + lane, step = share * 64;
-            for (int64_t t = t0 + first; t < t1; t += step) {
-                float2 p[3];
+    const int lane = lane_id(), wave = threadIdx.x >> 6, nv = a.views.n, v = v0 + wave / share;
+    double sS = 0.0, sL = 0.0, sD = 0.0;
+    if (wave < at_once * share && v < nv) {
+        const int64_t t0 = a.views[v].tile_base, t1 = v + 1 < nv ? a.views[v + 1].tile_base : a.n_tiles;
+        const int64_t b0 = a.views[v].depth_base, b1 = v + 1 < nv ? a.views[v + 1].depth_base : a.n_depth;
+        const int64_t first = (wave % share) * 64 + lane, step = share * 64;
+        for (int64_t t = t0 + first; t < t1; t += step) {
+            float2 p[3];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) p[c] = *reinterpret_cast<const float2 *>(a.partial + 2 * (c * a.n_tiles + t));
+            for (int c = 0; c < 3; ++c) p[c] = *reinterpret_cast<const float2 *>(a.partial + 2 * (c * a.n_tiles + t));
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    sS += p[c].x;
-                    sL += p[c].y;
-                }
+            for (int c = 0; c < 3; ++c) {
+                sS += p[c].x;
+                sL += p[c].y;
             }
-            if (a.has_depth)
-                for (int64_t b = b0 + first; b < b1; b += step) sD += a.depth_partial[b];
         }
-        sS = wave_sum_f64(sS);
-        sL = wave_sum_f64(sL);
-        sD = wave_sum_f64(sD);
-        if (lane == 0) {
-            red[0][wave] = sS;
-            red[1][wave] = sL;
-            red[2][wave] = sD;
-        }
-        __syncthreads();
-        const int u = v0 + (int)threadIdx.x;
-        if ((int)threadIdx.x < at_once && u < nv) {
-            const double npx = (double)a.views[u].W * (double)a.views[u].H;
-            sS = sL = sD = 0.0;
-            for (int i = 0; i < share; ++i) {
-                sS += red[0][threadIdx.x * share + i];
-                sL += red[1][threadIdx.x * share + i];
-                sD += red[2][threadIdx.x * share + i];
-            }
-            const double l1 = sL / (3.0 * npx), ssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
-            const double lv = (1.0 - a.lam) * l1 + a.lam * (1.0 - ssim) + (a.has_depth ? a.w_depth * ld : 0.0);
-            a.terms[u] = lv;
-            a.loss[4 * u] = (float)l1;
-            a.loss[4 * u + 1] = (float)ssim;
-            a.loss[4 * u + 2] = (float)ld;
-            a.loss[4 * u + 3] = (float)lv;
-        }
-        __syncthreads();
+        if (a.has_depth)
+            for (int64_t b = b0 + first; b < b1; b += step) sD += a.depth_partial[b];
     }
+    sS = wave_sum_f64(sS);
+    sL = wave_sum_f64(sL);
+    sD = wave_sum_f64(sD);
+    if (lane == 0) {
+        red[0][wave] = sS;
+        red[1][wave] = sL;
+        red[2][wave] = sD;
+    }
+    __syncthreads();
+    const int u = v0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < at_once && u < nv) {
+        const double npx = (double)a.views[u].W * (double)a.views[u].H;
+        sS = sL = sD = 0.0;
+        for (int i = 0; i < share; ++i) {
+            sS += red[0][threadIdx.x * share + i];
+            sL += red[1][threadIdx.x * share + i];
+            sD += red[2][threadIdx.x * share + i];
+        }
+        const double l1 = sL / (3.0 * npx), ssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
+        const double lv = (1.0 - a.lam) * l1 + a.lam * (1.0 - ssim) + (a.has_depth ? a.w_depth * ld : 0.0);
+        out[threadIdx.x] = lv;
+        a.loss[4 * u] = (float)l1;
+        a.loss[4 * u + 1] = (float)ssim;
+        a.loss[4 * u + 2] = (float)ld;
+        a.loss[4 * u + 3] = (float)lv;
+    }
+}
+
+// Calls of more views than one block takes at once: their terms, four views a block.
+constexpr int kTermViews = 4;
+__global__ __launch_bounds__(1024) void k_loss_views(FinalArgs a) {
+    const int v0 = (int)blockIdx.x * kTermViews;
+    view_terms(a, v0, kTermViews, 16 / kTermViews, a.terms + v0);
+}
+
+// One block of 16 waves: the terms of up to kArgViews views (of more, k_loss_views
+// has left them), L_iso, and the total in view order.  The total is one chain of
+// additions, so the terms are brought to LDS first.  With all views in rounds of
+// 16 in this block and the chain over memory, 1024 views of 64 x 48 took 273 us here
+// (the call 444 us; now 216, and 249 with two kernels before this one-pass loss).
+__global__ __launch_bounds__(1024) void k_loss_final(FinalArgs a) {
+    constexpr int kChunk = 1024;
+    __shared__ double terms[kChunk], red[16];
+    const int nv = a.views.n;
     double si = 0.0;
     for (int64_t b = threadIdx.x; b < a.n_iso_blocks; b += 1024) si += a.iso_partial[b];
     si = wave_sum_f64(si);
-    if (lane == 0) red[0][wave] = si;
-    __threadfence_block();  // the views' terms, read below by thread 0
-    __syncthreads();
+    if (lane_id() == 0) red[threadIdx.x >> 6] = si;
+    if (nv <= kArgViews) view_terms(a, 0, nv, 16 / nv, terms);
+    double total = 0.0;
+    for (int v0 = 0; v0 < nv; v0 += kChunk) {
+        const int n = nv - v0 < kChunk ? nv - v0 : kChunk;
+        __syncthreads();  // the chunk before is added up
+        if (nv > kArgViews && (int)threadIdx.x < n) terms[threadIdx.x] = a.terms[v0 + threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll 8
+            for (int v = 0; v < n; ++v) total += terms[v];
+        }
+    }
     if (threadIdx.x != 0) return;
-    double iso = 0.0, total = 0.0;
-    for (int w = 0; w < 16; ++w) iso += red[0][w];
+    double iso = 0.0;
+    for (int w = 0; w < 16; ++w) iso += red[w];
     iso = a.n_gauss > 0 ? (double)a.w_iso * iso / (3.0 * (double)a.n_gauss) : 0.0;
-    for (int v = 0; v < nv; ++v) total += a.terms[v];
     total += iso;
     a.loss[4 * nv] = (float)iso;
     a.loss[4 * nv + 1] = (float)total;
@@ -600,14 +623,29 @@ mgs_status loss_check(const int32_t *sizes, int32_t n_views, const float *rgb, c
 // of a call two and a half beyond their CU's share.  Measured: 641 x 479, 24.5 us
 // at 5 chunks, 22.4 at 6, 24.9 at 7, 33 at 13; 8 x 1200 x 680, 234 us at 8, 214 at
 // 13, 190 at 18, 182 at 20, 185 at 32.
-int ssim_chunks(const int32_t *sizes, int32_t n_views) {
+// room: host room for n_views entries.
+int ssim_chunks(const int32_t *sizes, int32_t n_views, LossView *room) {
+    // consecutive views of one height together, H with their strips: the views of a
+    // call mostly agree in size
+    int runs = 0;
+    for (int v = 0; v < n_views; ++v) {
+        const int32_t H = sizes[2 * v + 1];
+        if (runs == 0 || room[runs - 1].H != H) {
+            room[runs].H = H;
+            room[runs++].strips = 0;
+        }
+        room[runs - 1].strips += (sizes[2 * v] + kSC - 1) / kSC;
+    }
     int best = 4;
     double least = 0.0;
-    for (int nch = 4; nch <= 40; ++nch) {
+    // every choice costs the host 6 us for 4096 different heights: a few will do there
+    for (int nch = 4; nch <= 40; nch += runs > 256 ? 4 : 1) {
+        // ceil(H / rows), exact: half a row off a whole number, which is a hundred times
+        // what the float quotient can be off
+        const float rows = (float)(8 * nch - kWarm), per_row = 1.0f / rows, up = rows - 0.5f;
         int64_t blocks = 0;
-        for (int v = 0; v < n_views; ++v)
-            blocks += 3 * ceil_div(sizes[2 * v + 1], 8 * nch - kWarm) * ceil_div(sizes[2 * v], kSC);
-        const double cost = nch * std::max(3.0, (double)blocks / 256.0 + 2.5);
+        for (int r = 0; r < runs; ++r) blocks += (int64_t)room[r].strips * (int32_t)(((float)room[r].H + up) * per_row);
+        const double cost = nch * std::max(3.0, 3.0 * (double)blocks / 256.0 + 2.5);
         if (nch == 4 || cost < least) {
             least = cost;
             best = nch;
@@ -628,7 +666,7 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
                     const float *depth, const float *gt_depth, const float *scales, int64_t n_gauss,
                     const mgs_loss_opts *opts, LossView *views, void *ws, size_t ws_bytes, size_t *ws_required,
                     float *loss, float *dL_drgb, float *dL_ddepth, float *dL_dscales, void *stream) {
-    const int nch = ssim_chunks(sizes, n_views);
+    const int nch = ssim_chunks(sizes, n_views, views);
     int64_t tiles = 0, P = 0, squares = 0, n_depth = 0;
     for (int v = 0; v < n_views; ++v) {
         const int32_t W = sizes[2 * v], H = sizes[2 * v + 1];
@@ -746,6 +784,10 @@ mgs_status loss_run(const int32_t *sizes, int32_t n_views, const float *rgb, con
     f.has_depth = depth != nullptr;
     f.terms = at<double>(ws, off_terms);
     f.loss = loss;
+    if (n_views > kArgViews) {
+        k_loss_views<<<(unsigned)ceil_div(n_views, kTermViews), 1024, 0, s>>>(f);
+        MGS_LAUNCHED();
+    }
     k_loss_final<<<1, 1024, 0, s>>>(f);
     MGS_LAUNCHED();
     return MGS_OK;

@@ -217,3 +217,17 @@ def test_captured_call_of_89_views():
         torch.cuda.synchronize()
         for k in ("loss", "d_rgb", "d_depth"):
             assert torch.equal(getattr(ref, k), getattr(out, k)), k
+
+
+@pytest.mark.parametrize("n_views", [16, 17, 20, 1025])
+def test_loss_of_many_views(n_views):
+    """Up to 16 views are summed by the block that forms the total; of more, four a
+    block, and the total takes them 1024 at a time.  Every view against the oracle,
+    the heights all different in turn."""
+    sizes = [(3 + k % 11, 2 + k % 13) for k in range(n_views)]
+    rng = np.random.default_rng(19)
+    rgb, gt, d, gd = _images(rng, sizes)
+    scales = rng.uniform(0.01, 0.1, size=(1500, 3)).astype(np.float32)
+    print("case loss of", n_views, "views", flush=True)
+    res = mapping_loss(sizes, _flat(rgb), _flat(gt), _flat(d), _flat(gd), torch.from_numpy(scales).cuda(), 0.2, 0.7, 3.0)
+    _check(sizes, rgb, gt, d, gd, scales, 0.2, 0.7, 3.0, res)
