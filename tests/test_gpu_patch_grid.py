@@ -114,3 +114,22 @@ def test_launch_variants_match_oracle(W, H, patch, samples, n_kp):
     torch.cuda.synchronize()
     exp = PG.patch_grid_sample(cam, kp, kd, image, None, P=patch, min_kp=3, s=samples, opacity=0.5, scale_factor=0.5)
     _compare(None, res, exp, n_kp)
+
+
+@pytest.mark.parametrize("n_kp", [255, 256, 257, 258, 10837, 10838])
+def test_four_candidates_a_wave(n_kp):
+    """From 32768 candidates on, four times the keypoints at least, a wave takes four
+    of them: one less, remainders of 0, 1 and 2, and keypoints of a quarter and
+    more.  A third of the depth map is empty, so that a wave's four differ."""
+    W, H, P = 1016, 512, 8
+    rng = np.random.default_rng(n_kp)
+    cam = synth.Camera(W, H, 0.8 * W, 0.8 * W, W / 2.0, H / 2.0, np.eye(4, dtype=np.float32)[:3].copy())
+    kp = (rng.uniform(0, 1, (n_kp, 2)) ** 2 * [W, H]).astype(np.float32)
+    kd = np.where(rng.uniform(size=n_kp) < 0.3, rng.uniform(1, 3, n_kp), 0).astype(np.float32)
+    dm = np.where(rng.uniform(size=(H, W)) < 0.33, 0, rng.uniform(1, 3, (H, W))).astype(np.float32)
+    image = rng.uniform(0, 1, (3, H, W)).astype(np.float32)
+    print(f"case {n_kp} keypoints, {n_kp + 4 * (W // P) * (H // P)} candidates", flush=True)
+    res = patch_grid_sample(View.from_camera(cam), _t(kp), _t(kd), _t(image), _t(dm), patch=P, min_keypoints=3, samples=2)
+    torch.cuda.synchronize()
+    exp = PG.patch_grid_sample(cam, kp, kd, image, dm, P=P, min_kp=3, s=2, opacity=0.5, scale_factor=0.5)
+    _compare(None, res, exp, n_kp)
