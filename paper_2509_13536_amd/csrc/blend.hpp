@@ -100,16 +100,19 @@ __global__ __launch_bounds__(256) void k_bin_place(const uint2 *range, int64_t n
 // Both in one launch of one block, for calls with few bins (kPer a thread, their
 // lists' lengths kept in registers).  3225 bins of one 1200x680 view: 4.7 us
 // against 4.7 + 4.7 us, and 300 bins 2.3 us against 2.2 + 3.4; with eight a thread
-// (4270 bins) 8.0 us, no less than the two launches, which stay beyond 4096.
+// (4270 bins) 8.0 us, as long as the two launches, which stay beyond 8192.
 // With `totals` (the bins' counts and, at [n], that of the unused slots) it writes
-// the ranges too, of bin n as well.
-constexpr int64_t kBinOrderOneBlock = 4096;
+// the ranges too, of bin n as well.  longest (nullable): the longest list's length.
+constexpr int64_t kBinOrderFewBins = 4096, kBinOrderOneBlock = 8192;
 template <int kPer>
-__global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint2 *range, int n, uint32_t *order) {
+__global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint2 *range, int n, uint32_t *order,
+                                                    uint32_t *longest) {
     __shared__ uint32_t h[kOrderClasses];
     __shared__ uint32_t sums[16];
+    __shared__ uint32_t top;
     const int wave = (int)threadIdx.x >> 6, i0 = kPer * (int)threadIdx.x;
     if (threadIdx.x < kOrderClasses) h[threadIdx.x] = 0;
+    if (threadIdx.x == 0) top = 0;
     uint32_t len[kPer];
     if (totals) {
         uint32_t sum = 0;
@@ -133,10 +136,17 @@ __global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint
         }
     }
     __syncthreads();
+    uint32_t most = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k)
-        if (i0 + k < n) atomicAdd(&h[len_class(len[k])], 1u);
+        if (i0 + k < n) {
+            atomicAdd(&h[len_class(len[k])], 1u);
+            most = max(most, len[k]);
+        }
+    most = wave_max_u32(most);
+    if (lane_id() == 0) atomicMax(&top, most);
     __syncthreads();
+    if (longest && threadIdx.x == 0) *longest = top;
     // the classes' first slots
     const uint32_t c = threadIdx.x < kOrderClasses ? h[threadIdx.x] : 0u;
     const uint32_t incl = wave_incl_scan_u32(c);
@@ -428,6 +438,10 @@ struct BlendArgs {
     uint32_t *n_contrib;
     uint32_t *n_blend;  // per-pixel blended count (instrumented variant only)
     uint16_t *inst_qm;  // quadrant mask of every staged list entry, for the backward (nullable)
+    // both forms of the kernel are launched (not null): the split one does the work
+    // when the longest list has long_from entries, the other one when it has fewer
+    const uint32_t *longest;
+    uint32_t long_from;
 };
 
 // Staged Gaussian of a batch: image mean, scaled conic + log2 opacity, colour +
@@ -453,6 +467,8 @@ void k_blend_fwd(BlendArgs a) {
     using G = BinGeo<BTX, BTY, SPLIT>;
     constexpr int QX = G::QX, NQ = G::NQ;
     __shared__ Staged sh;
+    if constexpr (BTX * BTY == 1)
+        if (a.longest && (uniform_u32(*a.longest) >= a.long_from) != SPLIT) return;
     const int lane = threadIdx.x;
     int q = blockIdx.x & 7, tries = 0;
     // Without a pair that may reach the alpha clamp (the projection's flag),

@@ -60,7 +60,8 @@ namespace mgs {
 // from word CNT_Q on, 256 bytes apart so that no two share a cache line
 // counters[CNT_CLAMP] != 0: some visible pair may reach the 0.99 alpha clamp
 // within its tile rectangle (may_clamp), set by the projection
-enum { CNT_PV = 0, CNT_M = 2, CNT_KMIN = 4, CNT_KMAX = 5, CNT_CLAMP = 6, CNT_Q = 64, CNT_WORDS = CNT_Q + 8 * kQueueStride };
+// counters[CNT_LONGEST]: the longest bin list, where a forward's form depends on it
+enum { CNT_PV = 0, CNT_M = 2, CNT_KMIN = 4, CNT_KMAX = 5, CNT_CLAMP = 6, CNT_LONGEST = 7, CNT_Q = 64, CNT_WORDS = CNT_Q + 8 * kQueueStride };
 
 __global__ void k_init(uint32_t *counters) {
     for (int i = threadIdx.x; i < CNT_WORDS; i += blockDim.x) counters[i] = 0;
@@ -1282,38 +1283,53 @@ bool box_cull() {
 // A call with few bins splits each 16x16 bin into its four quadrants, one wave
 // each: four times the waves, one evaluation per visit, in the forward the same
 // bits (k_blend_fwd SPLIT, k_blend_bwd_split).  MGS_BLEND_SPLIT=0 or 1 forces
-// either.  While the bins hardly outnumber the resident waves (6144), the longest
-// list alone sets the time.  Forward calls, one wave a bin against four, us: 4800
-// bins of a room of 500k Gaussians 477 / 384, of a surface 925 / 849; 6450 bins
-// 356 / 337, 730 / 558 with 1M, 538 / 543; 7200 bins 547 / 484, 1231 / 1190; 9675
-// bins 401 / 412, 818 / 719, 720 / 741; 12900 bins 451 / 489, 893 / 930.  The
-// split backward pays for four staged copies of each list and a fold over the
-// waves; from a split forward on, forward and backward together: 4800 bins 892 /
-// 832, 1670 / 1890; 6450 bins 661 / 668, 1004 / 1152; 9675 bins 794 / 903.
-constexpr int64_t kSplitFwdBelowBins = 8192, kSplitBwdBelowBins = 4096;
-bool split_blend(int btx, int bty, int64_t n_bins, int64_t below) {
+// either.  Below 4096 bins the one-wave kernels leave much of the chip idle.
+// From there to 8191 bins it depends on the lists whether a forward gains: four
+// waves stage each list, which costs where all lists are alike (a box of Gaussians,
+// one wave a bin against four, us: 4800 bins 253 / 294, 6450 288 / 330, 7500 299 /
+// 353), but the longest list alone is a shorter chain (a room of 500k: 419 / 353,
+// 410 / 382; 6424 bins of mixed resolutions 595 / 380).  So both kernels are
+// launched there, and the longest list, which k_bin_order finds, picks the one that
+// works (the other one exits, 3 us).  The split backward pays for four staged
+// copies of each list and a fold over the waves, so it stays below 4096: forward
+// and backward together from a split forward on, 4800 bins 892 / 832, 1670 / 1890;
+// 6450 bins 661 / 668, 1004 / 1152; 9675 bins 794 / 903.
+constexpr int64_t kSplitBelowBins = 4096, kSplitChoiceBelowBins = 8192;
+// -1: as the bins count says
+int split_forced() {
+    const char *e = getenv("MGS_BLEND_SPLIT");
+    return e && (e[0] == '0' || e[0] == '1') ? e[0] - '0' : -1;
+}
+bool split_blend(int btx, int bty, int64_t n_bins) {
     if (btx != 1 || bty != 1) return false;
-    if (const char *e = getenv("MGS_BLEND_SPLIT")) {
-        if (e[0] == '0') return false;
-        if (e[0] == '1') return true;
-    }
-    return n_bins < below;
+    const int forced = split_forced();
+    return forced >= 0 ? forced == 1 : n_bins < kSplitBelowBins;
+}
+// A split forward of M entries, not few bins, gains when the longest list holds more
+// than a SIMD's share of them, and is long enough for the chain to outweigh the
+// staging.  Its time over the other form's, by the longest list, M and the share's
+// multiple: 2962, 1.09M, 2.8: 0.73; 1002, 366k, 2.8: 0.76; 1057, 730k, 1.48: 0.96; 1357, 1.25M,
+// 1.11: 1.00; 1248, 1.11M, 1.15: 1.01.  Just outside: 797, 546k, 1.50: 1.00; 922,
+// 701k, 1.35: 1.05; 947, 435k, 2.2 (gains) 0.81; 8011, 8.8M, 0.94: 1.06; 4463, 5.3M, 0.87 (gains) 0.80.
+uint32_t split_from_length(int64_t M) {
+    return (uint32_t)std::max(1.0, std::max((double)M / 1024.0, 1.17 * std::sqrt((double)M)));
 }
 
 template <int ROUNDS, int BINS>
 void launch_binsort_as(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask, int bits, uint32_t bins,
-                           int stride, uint32_t *table, uint2 *range, uint32_t *order, hipStream_t s) {
+                           int stride, uint32_t *table, uint2 *range, uint32_t *order, uint32_t *longest,
+                           hipStream_t s) {
     const unsigned nb = (unsigned)binsort_blocks(M);
     k_binsort_hist<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, M, mask, bins, stride, table);
     k_binsort_columns<<<(unsigned)(stride / 32), 1024, 0, s>>>(table, nb, stride);
-    k_bin_order<(BINS > kBinSortMidBins ? 8 : 4)><<<1, 1024, 0, s>>>(table + (int64_t)nb * stride, range, (int)bins, order);
+    k_bin_order<(BINS > kBinSortMidBins ? 8 : 4)><<<1, 1024, 0, s>>>(table + (int64_t)nb * stride, range, (int)bins, order, longest);
     k_binsort_scatter<ROUNDS, BINS><<<nb, kBinSortThreads, 0, s>>>(in, out, M, mask, bits, bins, stride, table, range);
 }
 void launch_binsort(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask, int bits, uint32_t bins, int stride,
-                    uint32_t *table, uint2 *range, uint32_t *order, hipStream_t s) {
+                    uint32_t *table, uint2 *range, uint32_t *order, uint32_t *longest, hipStream_t s) {
     auto go = [&](auto rounds, auto cap) {
         launch_binsort_as<decltype(rounds)::value, decltype(cap)::value>(in, out, M, mask, bits, bins, stride, table,
-                                                                         range, order, s);
+                                                                         range, order, longest, s);
     };
     auto by_rounds = [&](auto cap) {
         switch (binsort_rounds(M)) {
@@ -1742,6 +1758,9 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     // stable tile sort on the bin field.  Wide: the values start as the
     // emission index, so at least one pass.
     uint32_t *bin_order = at<uint32_t>(ws, L.bin_order);
+    const bool choose_split = S.btx == 1 && S.bty == 1 && split_forced() < 0 && S.B_total >= kSplitBelowBins &&
+                              S.B_total < kSplitChoiceBelowBins;
+    uint32_t *longest = choose_split ? counters + CNT_LONGEST : nullptr;
     int ic = 0;
     const bool one_pass = packed && M > 0 && S.B_total < kBinSortMaxBins &&
                           binsort_words(M, S.B_total) <= (int64_t)((L.iv1 - L.iv0) / 4) + M;
@@ -1750,7 +1769,7 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     if (one_pass) {
         const uint32_t mask = (uint32_t)((1ull << tbits) - 1);
         launch_binsort(it[0], it[1], M, mask, bits_for(S.B_total + 1), (uint32_t)S.B_total, bstride, table, range,
-                       bin_order, s);
+                       bin_order, longest, s);
         ic = 1;
     }
     for (int sh = 0; sh < tbits && M > 0 && !one_pass; sh += 8) {
@@ -1773,8 +1792,11 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
                                                        S.B_total, range);
     if (S.B_total > 0 && !one_pass) {
         uint32_t *book = reinterpret_cast<uint32_t *>(range + S.B_total);
-        if (S.B_total <= kBinOrderOneBlock) {
-            k_bin_order<4><<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order);
+        static_assert(kSplitChoiceBelowBins <= kBinOrderOneBlock, "the longest list");
+        if (S.B_total <= kBinOrderFewBins) {
+            k_bin_order<4><<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order, longest);
+        } else if (S.B_total <= kBinOrderOneBlock) {
+            k_bin_order<8><<<1, 1024, 0, s>>>(nullptr, range, (int)S.B_total, bin_order, longest);
         } else {
             k_bin_count<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book);
             k_bin_place<<<bin_order_grid(S.B_total), 256, 0, s>>>(range, S.B_total, book, bin_order);
@@ -1804,14 +1826,18 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
     ba.out_T = out_T;
     ba.n_contrib = at<uint32_t>(ws, L.n_contrib);
     ba.n_blend = at<uint32_t>(ws, L.n_blend);
-    const bool split = split_blend(S.btx, S.bty, S.B_total, kSplitFwdBelowBins);
+    const bool split = split_blend(S.btx, S.bty, S.B_total);
+    ba.longest = longest;
+    ba.long_from = split_from_length(M);
     // the one-wave forward of a backward call over bins of several tiles keeps
     // its quadrant masks for the backward (the same bins, the same decisions)
     ba.inst_qm = bwd && !split && S.btx * S.bty > 1 ? at<uint16_t>(ws, L.inst_qm) : nullptr;
-    const int64_t grid = blend_grid(split ? 4 * S.B_total : S.B_total);
     timer.mark();  // 2
-    launch_blend_fwd(opts && opts->count_blended, split, S.btx, S.bty, (unsigned)grid, s, ba);
-    MGS_LAUNCHED();
+    for (int form = choose_split ? 0 : (int)split; form <= (choose_split ? 1 : (int)split); ++form) {
+        const int64_t grid = blend_grid(form ? 4 * S.B_total : S.B_total);
+        launch_blend_fwd(opts && opts->count_blended, form, S.btx, S.bty, (unsigned)grid, s, ba);
+        MGS_LAUNCHED();
+    }
     timer.mark();  // 3
     static const int spans[4][3] = {{0, 0, 1}, {1, 1, 2}, {2, 2, 3}, {3, 0, 3}};
     timer.finish(spans, 4);
@@ -1883,7 +1909,7 @@ extern "C" mgs_status mgs_render_backward(const mgs_gaussians *maps, int32_t n_m
     for (int m = 0; m < n_maps; ++m)
         if (S.maps[m].sh_degree != 0) pose_blend = false;
     // few bins: four-wave blocks, one per bin, four to a CU (their registers)
-    const bool split = split_blend(S.btx, S.bty, S.B_total, kSplitBwdBelowBins);
+    const bool split = split_blend(S.btx, S.bty, S.B_total);
     const int64_t grid = split ? std::max<int64_t>(1, std::min<int64_t>(S.B_total, (int64_t)num_cus() * 4))
                                : blend_grid(S.B_total);
     launch_blend_bwd(split, S.btx, S.bty, (unsigned)grid, s, bb, pose_blend);

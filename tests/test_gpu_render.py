@@ -616,3 +616,49 @@ def test_bin_sort_of_many_bins(n, W, H):
     st = run_forward(sc)
     assert_keys_and_lists(sc, sc.cams[0], st)
     image_parity(sc, sc.cams[0], st)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("W,H", [(1024, 1024), (1024, 2032)])
+@pytest.mark.parametrize("crowd", [False, True])
+def test_forward_form_by_the_longest_list(W, H, crowd, wide, monkeypatch):
+    """From 4096 to 8191 bins the longest list picks the forward's form: lists all
+    alike, and a crowd on one spot whose list is longer than a SIMD's share of the
+    entries.  Whichever form works, with either key format: every pixel drawn, the
+    bits of both forced forms."""
+    if wide:
+        monkeypatch.setenv("MGS_WIDE_INSTANCES", "1")
+    sc = synth.tiny_scene(3000, W, H, 79, log_scale_mu=-3.5)
+    if crowd:
+        sc.means[:2500, :2] = 0.02 * sc.means[:2500, :2] * sc.means[:2500, 2:]
+        sc.scales[:2500] = 0.01
+    print(f"case {W}x{H} crowd {crowd} wide {wide}", flush=True)
+    m = GaussianMap.from_numpy(sc)
+    out = []
+    for forced in (None, "0", "1"):
+        if forced is not None:
+            monkeypatch.setenv("MGS_BLEND_SPLIT", forced)
+        st = render_forward([m], [View.from_camera(sc.cams[0], 0)], count_blended=True)
+        torch.cuda.synchronize()
+        out.append((st.rgb, st.depth, st.T, st.ws.view(st.info.off_n_contrib, W * H, torch.int32).clone(),
+                    st.ws.view(st.info.off_n_blend, W * H, torch.int32).clone()))
+        rng = st.ws.view(st.info.off_bin_range, 2 * int(st.info.n_bins), torch.int32).view(-1, 2)
+        longest, M = int((rng[:, 1] - rng[:, 0]).max()), int(st.info.n_instances)
+        assert (longest >= max(M / 1024, 1.17 * M ** 0.5)) == crowd, (longest, M)
+    for forced in out[1:]:
+        for x, y in zip(out[0], forced):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("W,H,bins", [(1024, 1024, 4096), (1024, 1025, 4160), (2048, 1024, 8192), (2048, 1040, 8320)])
+def test_bin_order_from_ranges(W, H, bins, monkeypatch):
+    """Wide keys take radix passes, after which one block orders up to 4096 bins four
+    a thread and up to 8192 eight, and two launches more: the order holds every bin
+    once (each pixel is drawn), by falling class of length."""
+    monkeypatch.setenv("MGS_WIDE_INSTANCES", "1")
+    monkeypatch.setenv("MGS_BIN_TILES", "1x1")
+    sc = synth.tiny_scene(2000, W, H, 47, log_scale_mu=-3.0)
+    print(f"case {W}x{H}", flush=True)
+    st = run_forward(sc)
+    assert int(st.info.n_bins) == bins and int(st.info.inst_bin_bits) == 0
+    image_parity(sc, sc.cams[0], st)
