@@ -1,7 +1,7 @@
 // Stable sort of the packed instance keys by their bin, in one counting pass
 // over all bins, for calls whose bins' counters fit a block's LDS.  Four
-// launches, the last two of which also give every bin's range of the list and
-// the blend's work order:
+// launches, of which the third also gives every bin's range of the list and the
+// blend's work order:
 //   k_binsort_hist     per block of consecutive instances: its count per bin
 //   k_binsort_columns  per bin: exclusive scan of the blocks' counts, the total
 //   k_bin_order        the bins' ranges from the totals, and the work order
@@ -22,27 +22,40 @@
 namespace mgs {
 
 constexpr int kBinSortThreads = 512, kBinSortWaves = kBinSortThreads / 64;
-// With the bin of unused slots: 128 KB of 16-bit counters, one block on a CU, whose
-// bases no longer fit beside them and are gathered (1.1M instances over 4270 bins:
-// 42 us for the four launches against 57 for the radix passes, ranges and order).
-// Up to kBinSortMidBins they are 64 KB and 16 KB of bases, two blocks on a CU, up
-// to kBinSortFewBins half of that.
-constexpr int64_t kBinSortMaxBins = 8192;
-
+// Counters of 16 bits, a row a wave, with the bin of unused slots.  Up to
+// kBinSortFewBins they take 32 KB and the blocks' bases 8 KB, up to kBinSortMidBins
+// twice that, two blocks on a CU.  Beyond, they are 104 KB, one block on a CU, whose
+// bases no longer fit beside them and are gathered.  The time of a call's binning and
+// sorting against that with radix passes: below 4096 bins 0.72 to 0.98 at every
+// size from 500 to 49M instances.  Beyond, in calls of 2^17 to 2^22 instances: 4352 bins 0.88 to
+// 0.97, 5400 0.91 to 0.99, 6450 0.92 to 0.99, 7500 0.97 to 1.04; of more, 4352 bins 0.95
+// to 1.03, 6450 1.01 to 1.08, 8085 1.05 to 1.21.
+constexpr int64_t kBinSortMaxBins = 6656, kBinSortManyMax = int64_t(1) << 22;
 constexpr int kBinSortFewBins = 2048, kBinSortMidBins = 4096;
 constexpr int kBinSortBits = 13;
-static_assert(kBinSortMaxBins == int64_t(1) << kBinSortBits, "a bin's bits");
+static_assert(kBinSortMaxBins <= int64_t(1) << kBinSortBits, "a bin's bits");
 
 // Rounds of 64 instances a wave takes: many where the table of counts (a row a
 // block) has to stay small against the instances, few where the blocks have to
-// fill the chip.  All launches together at 2 / 4 / 8 / 16 rounds, us: 96k
-// instances over 1131 bins 12.6 / 13.1 / 16.2 / 22, 5.3M over 1200 89 / 66 / 58 /
-// 61, 6.9M over 3225 - / 104 / 79 / 79; 1.1M at 16 rounds would be 139 blocks.
-inline int binsort_rounds(int64_t m) { return m < (int64_t(1) << 17) ? 2 : m < (int64_t(1) << 22) ? 8 : 16; }
+// fill the chip.  A call's binning and sorting at 2 / 8 / 16 rounds, us: 40k instances
+// over 1200 bins 39 / 43 / 50, 260k 69 / 72 / 78, 917k 85 / 82 / 88; 2.9M over 3225
+// bins - / 118 / 120, 4.6M over 1200 172 / 151 / 154, 12M over 3225 - / 257 / 261, 24M - / 471 / 440, 49M
+// - / 880 / 816.  (2 rounds would serve up to 2^19, but leave no room for the table
+// of 2048 bins and more.)
+inline int binsort_rounds(int64_t m) { return m < (int64_t(1) << 17) ? 2 : m < (int64_t(1) << 24) ? 8 : 16; }
 inline int64_t binsort_blocks(int64_t m) { return ceil_div(m, kBinSortThreads * binsort_rounds(m)); }
 inline int64_t binsort_stride(int64_t bins) { return (bins + 1 + 63) / 64 * 64; }
 // words of the table of counts, with the row of totals after it
 inline int64_t binsort_words(int64_t m, int64_t bins) { return (binsort_blocks(m) + 1) * binsort_stride(bins); }
+// Whether a call of m packed instances takes this sort.  The table has to fit
+// `room` words, the value arrays that such keys leave unused, about 2 m: from 2^17
+// instances on it does at any of these bins, below them up to 1983 bins (128
+// words for 64 instances, 31 thousand instances at 1983 bins).
+inline bool binsort_takes(int64_t m, int64_t bins, int64_t room) {
+    if (m <= 0 || bins >= kBinSortMaxBins || (bins >= kBinSortMidBins && m >= kBinSortManyMax)) return false;
+    if (binsort_rounds(m) == 2 && binsort_stride(bins) > kBinSortFewBins) return false;
+    return binsort_words(m, bins) <= room;
+}
 
 // bin of a key: unused slots hold all ones there and count as bin n_bins
 __device__ __forceinline__ uint32_t binsort_bin(uint32_t low, uint32_t mask, uint32_t n_bins) {

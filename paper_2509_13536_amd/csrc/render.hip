@@ -1331,16 +1331,23 @@ void launch_binsort(const uint64_t *in, uint64_t *out, int64_t M, uint32_t mask,
         launch_binsort_as<decltype(rounds)::value, decltype(cap)::value>(in, out, M, mask, bits, bins, stride, table,
                                                                          range, order, longest, s);
     };
-    auto by_rounds = [&](auto cap) {
-        switch (binsort_rounds(M)) {
-            case 2: go(std::integral_constant<int, 2>{}, cap); break;
-            case 8: go(std::integral_constant<int, 8>{}, cap); break;
-            default: go(std::integral_constant<int, 16>{}, cap); break;
-        }
-    };
-    if (stride <= kBinSortFewBins) by_rounds(std::integral_constant<int, kBinSortFewBins>{});
-    else if (stride <= kBinSortMidBins) by_rounds(std::integral_constant<int, kBinSortMidBins>{});
-    else by_rounds(std::integral_constant<int, (int)kBinSortMaxBins>{});
+    using R2 = std::integral_constant<int, 2>;
+    using R8 = std::integral_constant<int, 8>;
+    using R16 = std::integral_constant<int, 16>;
+    using Few = std::integral_constant<int, kBinSortFewBins>;
+    using Mid = std::integral_constant<int, kBinSortMidBins>;
+    using Many = std::integral_constant<int, (int)kBinSortMaxBins>;
+    const int rounds = binsort_rounds(M);  // the forms that binsort_takes lets through
+    if (stride <= kBinSortFewBins) {
+        if (rounds == 2) go(R2{}, Few{});
+        else if (rounds == 8) go(R8{}, Few{});
+        else go(R16{}, Few{});
+    } else if (stride <= kBinSortMidBins) {
+        if (rounds == 8) go(R8{}, Mid{});
+        else go(R16{}, Mid{});
+    } else {
+        go(R8{}, Many{});
+    }
 }
 
 void launch_blend_fwd(bool count, bool split, int btx, int bty, unsigned grid, hipStream_t s, const BlendArgs &ba) {
@@ -1762,8 +1769,7 @@ extern "C" mgs_status mgs_render_forward(const mgs_gaussians *maps, int32_t n_ma
                               S.B_total < kSplitChoiceBelowBins;
     uint32_t *longest = choose_split ? counters + CNT_LONGEST : nullptr;
     int ic = 0;
-    const bool one_pass = packed && M > 0 && S.B_total < kBinSortMaxBins &&
-                          binsort_words(M, S.B_total) <= (int64_t)((L.iv1 - L.iv0) / 4) + M;
+    const bool one_pass = packed && binsort_takes(M, S.B_total, (int64_t)((L.iv1 - L.iv0) / 4) + M);
     uint32_t *table = iv[0];  // and on through iv[1]: packed keys have no values
     const int bstride = (int)binsort_stride(S.B_total);
     if (one_pass) {

@@ -662,3 +662,40 @@ def test_bin_order_from_ranges(W, H, bins, monkeypatch):
     st = run_forward(sc)
     assert int(st.info.n_bins) == bins and int(st.info.inst_bin_bits) == 0
     image_parity(sc, sc.cams[0], st)
+
+
+@pytest.mark.parametrize("n,W,H,scale,rounds,one_pass", [
+    (200, 16, 16, -3.0, 2, True), (900, 704, 720, -2.6, 2, True), (500, 992, 512, -2.6, 2, False),
+    (2500, 704, 720, -2.8, 8, True), (8000, 1008, 1040, -3.3, 8, True), (8000, 1024, 1024, -3.3, 8, True),
+    (8000, 880, 1936, -3.3, 8, True), (8000, 1024, 1664, -3.3, 8, False), (40_000, 1024, 1024, -2.5, 8, False),
+    (100_000, 704, 720, -2.2, 16, True), (100_000, 1008, 1040, -2.2, 16, True)])
+def test_bin_sort_routes(n, W, H, scale, rounds, one_pass, monkeypatch):
+    """Each form of the one-pass bin sort (2, 8 and 16 rounds a wave; 2048, 4096 and
+    6656 counters) at the last bins of its range, and the calls just outside that
+    take radix passes: 1984 bins of few instances, 6656 bins, 4096 bins of 2^22
+    instances and more.  The lists are those of the wide keys, which take radix
+    passes at any size."""
+    sc = synth.tiny_scene(n, W, H, 83, log_scale_mu=scale)
+    m, view, lists = GaussianMap.from_numpy(sc), View.from_camera(sc.cams[0], 0), []
+    for wide in (False, True):
+        if wide:
+            monkeypatch.setenv("MGS_WIDE_INSTANCES", "1")
+        st = render_forward([m], [view])
+        torch.cuda.synchronize()
+        info, bins, M = st.info, int(st.info.n_bins), int(st.info.n_instances)
+        tb, rb = int(info.inst_bin_bits), int(info.inst_rank_bits)
+        assert (tb == 0) == wide
+        rng = st.ws.view(info.off_bin_range, 2 * bins, torch.int32).view(-1, 2)
+        key = st.ws.view(info.off_inst_key, M, torch.int64)[:int(rng.max())]
+        # of an empty bin the range's place is not specified
+        lists.append((rng[:, 1] - rng[:, 0], *((key >> 32, key & 0xFFFFFFFF) if wide else (key & (1 << tb) - 1, key >> tb & (1 << rb) - 1))))
+        if wide:
+            continue
+        print(f"case {n} Gaussians, {W}x{H}: {M} instances, {bins} bins", flush=True)
+        assert rounds == (2 if M < 1 << 17 else 8 if M < 1 << 24 else 16)
+        table = (-(-M // (512 * rounds)) + 1) * (-(-(bins + 1) // 64) * 64)
+        assert one_pass == (bins < 6656 and (bins < 4096 or M < 1 << 22) and table <= -(-M // 64) * 64 + M)
+        if bins > 255 and M > 80_000:  # two radix passes end in the other buffer, 8 bytes an instance further from the ranges
+            assert one_pass == (int(info.off_bin_range - info.off_inst_key) < 21 * M)
+    for x, y in zip(*lists):
+        assert torch.equal(x, y)
