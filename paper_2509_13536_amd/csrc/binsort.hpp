@@ -161,8 +161,10 @@ __global__ __launch_bounds__(kBinSortThreads) void k_binsort_scatter(const uint6
         }
         const uint64_t peers = (uint64_t)phi << 32 | plo;
         const uint32_t before = cnt[d];
+        wave_lds_sync();
         rank[r] = before + (uint32_t)__popcll(peers & lt);
         if (valid && (peers & ~lt) >> lane == 1ull) cnt[d] = (Count)(rank[r] + 1u);  // the last of its bin
+        wave_lds_sync();
     }
     __syncthreads();
     // where the block's part of each bin begins, and each wave's in it

@@ -1131,13 +1131,6 @@ __device__ __forceinline__ int64_t next_item_thread(uint32_t *queues, int64_t n_
     return -1;
 }
 
-// LDS written by lanes of this wave, then read by other lanes of it
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <bool POSE>
 __global__ __launch_bounds__(256, 4) void k_blend_bwd_split(BlendBwdArgs a) {
     using G = BinGeo<1, 1, true>;

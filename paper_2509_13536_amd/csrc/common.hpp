@@ -107,6 +107,15 @@ __device__ __forceinline__ float readlane_f(float x, int l) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
 }
 
+// Between LDS accesses of some lanes of a wave and the accesses of other lanes of it
+// to the same words.  A wave's LDS accesses are done in their order, so it is
+// no instruction: it holds the compiler to that order.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uint32_t, x); }
 
 // ---------------------------------------------------------------- host helpers

@@ -122,13 +122,6 @@ __device__ __forceinline__ void static_for(F &&f) {
     }
 }
 
-// LDS written by lanes of this wave, then read by other lanes of it
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ int uniform_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // acc[m] += w[K - m] v for a group's four outputs

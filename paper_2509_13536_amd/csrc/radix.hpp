@@ -158,8 +158,10 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(const K *keys_i
         dg[r] = valid ? d : 0xFFFFFFFFu;
         const uint64_t peers = match_digit(d, valid);
         const uint32_t before = wcnt[wave][d];
+        wave_lds_sync();
         rank[r] = before + (uint32_t)__popcll(peers & lt_mask);
         if (valid && (int)(__ffsll((long long)peers) - 1) == lane) wcnt[wave][d] = before + (uint32_t)__popcll(peers);
+        wave_lds_sync();
     }
     __syncthreads();
     {

@@ -614,7 +614,7 @@ __global__ __launch_bounds__(64 * kRankWaves) void k_rank_pairs(const uint32_t *
     }
 #pragma unroll
     for (int r = 0; r < kLoads; ++r) mine[32 * r + item] = k[r];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     uint32_t rank = 0;
     for (int q = 0; q < per; q += kRankStep) {
         uint4 c[kRankStep / 4];
