@@ -60,7 +60,7 @@ struct SsimArgs {
     int64_t n_tiles;  // per channel
     int nch;          // column chunks of a tile
     const float *rgb, *gt;
-    float *partial;   // [3][n_tiles][2]: SSIM sum, |x - y| sum
+    float *partial;   // [3][n_tiles][2]: sum of 1 - SSIM, of |x - y|
     float *d_rgb;
     float lam;
     float w[kLW];     // normalised window weights
@@ -71,7 +71,7 @@ __device__ __forceinline__ float sgnf(float d) { return d > 0.0f ? 1.0f : (d < 0
 // ---------------------------------------------------------------- colour: SSIM and L1
 // A block of four waves takes a strip of 54 output columns of one channel and
 // marches down its rows in chunks of 8.  The window is needed twice: over the
-// moments E[x], E[y], E[x^2 + y^2], E[xy] (the variances enter only as their
+// moments E[x], E[y], E[(x - y)^2], E[xy] (the variances enter only as their
 // sum) and over the three derivative maps.  Both filters are carried along the
 // march, so the maps never leave the chip: memory sees x and y once (their halo
 // again through the caches) and the gradient.
@@ -263,7 +263,7 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
             if (out_own) {
                 const float o0 = map[0][row_at(r) + lane], o1 = map[1][row_at(r) + lane], o2 = map[2][row_at(r) + lane];
                 const float d = xo[u] - yo[u];
-                const float gs = __builtin_fmaf(yo[u], o2, __builtin_fmaf(2.0f * xo[u], o1, o0));
+                const float gs = o0 + (2.0f * xo[u] * o1 + yo[u] * o2);  // no FMA: 0 of equal images
                 a.d_rgb[cbase + (int64_t)oy * W + ox] = __builtin_fmaf(-ks, gs, kl1 * sgnf(d));
                 sL += fabsf(d);
             }
@@ -284,7 +284,7 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
                     const f4 p = quad(x, kc), q = quad(y, kc);
                     f4 e;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) e[i] = __builtin_fmaf(p[i], p[i], q[i] * q[i]);
+                    for (int i = 0; i < 4; ++i) e[i] = (p[i] - q[i]) * (p[i] - q[i]);
                     return e;
                 }, v);
             } else {
@@ -317,16 +317,18 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
                 const int gy = r0 - kLR + 8 * j - 12 + 2 * w + u;  // uniform
                 const bool in = col_in && gy >= 0 && gy < H;
                 const float mx = mx2[u], my = my2[u], e = e2[u], p = p2[u];
-                const float mxy = mx * my, q = __builtin_fmaf(mx, mx, my * my);
-                const float A = __builtin_fmaf(2.0f, mxy, kC1), B = __builtin_fmaf(2.0f, p - mxy, kC2);
-                const float iC = __builtin_amdgcn_rcpf(q + kC1), iD = __builtin_amdgcn_rcpf((e - q) + kC2);
-                const float i2 = iC * iD;
-                const float S = A * B * i2;
-                const float d0 = 2.0f * __builtin_fmaf(my * (B - A), i2, mx * S * (iD - iC));
+                // SSIM = (1 - a) (1 - b), a and b differences of the two images over sums,
+                // so that equal windows give 1, no first derivative, and the second and
+                // third to a factor of -2, exactly; 1 - SSIM keeps its small values
+                const float dm = mx - my, dd = dm * dm, ed = e - dd;
+                const float iC = __builtin_amdgcn_rcpf(__builtin_fmaf(mx, mx, my * my) + kC1);
+                const float iD = __builtin_amdgcn_rcpf(__builtin_fmaf(2.0f, __builtin_fmaf(-mx, my, p), ed) + kC2);
+                const float a1 = dd * iC, b1 = ed * iD, u1 = 1.0f - a1, v1 = 1.0f - b1, uD = u1 * iD;
+                const float d0 = 2.0f * __builtin_fmaf(v1 * iC, __builtin_fmaf(-mx, u1, my), uD * __builtin_fmaf(mx, v1, -my));
                 M[0][u] = in ? d0 : 0.0f;
-                M[1][u] = in ? -S * iD : 0.0f;
-                M[2][u] = in ? 2.0f * A * i2 : 0.0f;
-                if (gy >= r0 && gy < rend) sS += col_own ? S : 0.0f;
+                M[1][u] = in ? -uD * v1 : 0.0f;
+                M[2][u] = in ? 2.0f * uD : 0.0f;
+                if (gy >= r0 && gy < rend) sS += col_own ? __builtin_fmaf(-a1, b1, a1 + b1) : 0.0f;
             }
 #pragma unroll
             for (int k = 0; k < 3; ++k) *reinterpret_cast<f2 *>(map[k] + at_col + 2 * w) = M[k];
@@ -533,11 +535,11 @@ __device__ __forceinline__ void view_terms(const FinalArgs &a, int v0, int at_on
             sL += red[1][threadIdx.x * share + i];
             sD += red[2][threadIdx.x * share + i];
         }
-        const double l1 = sL / (3.0 * npx), ssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
-        const double lv = (1.0 - a.lam) * l1 + a.lam * (1.0 - ssim) + (a.has_depth ? a.w_depth * ld : 0.0);
+        const double l1 = sL / (3.0 * npx), dssim = sS / (3.0 * npx), ld = a.has_depth ? sD / npx : 0.0;
+        const double lv = (1.0 - a.lam) * l1 + a.lam * dssim + (a.has_depth ? a.w_depth * ld : 0.0);
         out[threadIdx.x] = lv;
         a.loss[4 * u] = (float)l1;
-        a.loss[4 * u + 1] = (float)ssim;
+        a.loss[4 * u + 1] = (float)(1.0 - dssim);
         a.loss[4 * u + 2] = (float)ld;
         a.loss[4 * u + 3] = (float)lv;
     }

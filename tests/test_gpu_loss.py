@@ -231,3 +231,25 @@ def test_loss_of_many_views(n_views):
     print("case loss of", n_views, "views", flush=True)
     res = mapping_loss(sizes, _flat(rgb), _flat(gt), _flat(d), _flat(gd), torch.from_numpy(scales).cuda(), 0.2, 0.7, 3.0)
     _check(sizes, rgb, gt, d, gd, scales, 0.2, 0.7, 3.0, res)
+
+
+def test_equal_pixels_have_no_gradient():
+    """Where both images agree over the two windows around a pixel, SSIM there is 1 and
+    the gradient 0, exactly: an optimiser that divides by a gradient's own size would
+    make a full step of a rounding.  Background, flat and textured parts."""
+    W, H = 163, 105
+    rng = np.random.default_rng(21)
+    y = rng.uniform(0, 1, (3, H, W))
+    y[:, :40, :70] = 0.0
+    y[:, 50:80, 60:110] = 0.7
+    x = y.copy()
+    same = _flat([x.astype(np.float32)])
+    print("case equal images", flush=True)
+    res = mapping_loss([(W, H)], same, same.clone(), lambda_ssim=0.2)
+    assert res.loss[1] == 1.0 and res.loss[-1] == 0.0 and not res.d_rgb.any()
+    x[:, 60:64, 140:150] += 0.2
+    res = mapping_loss([(W, H)], _flat([x.astype(np.float32)]), same, lambda_ssim=0.2)
+    g = res.d_rgb.view(3, H, W).clone()
+    assert g[:, 60:64, 140:150].ne(0).all()
+    g[:, 50:74, 130:160] = 0
+    assert not g.any()
