@@ -1088,8 +1088,9 @@ __global__ __launch_bounds__(64) void k_blend_bwd(BlendBwdArgs a) {
 // With one pixel a lane, all ten values of a visit are products of two, gp and
 // alpha T, with the pixel's offset and its upstream gradient.  So a visit leaves
 // just these two in LDS, and after kDefer visits the wave forms all sums at once:
-// lane 8 f + r takes row r of visit f's quadrant, eight pixels, whose gradients it
-// keeps in registers, and three DPP steps add the rows.  A wave here is bound by
+// lane 8 f + k takes eight pixels of visit f's quadrant, two neighbours in each of
+// four alternate rows, whose gradients it keeps in registers, and three DPP steps add
+// the eight lanes.  A wave here is bound by
 // the number of its instructions (one alone issues one in seven cycles, and the
 // longest lists set the time): 16 a visit and two LDS accesses in place of 45
 // with the ten values folded by swaps.

@@ -76,12 +76,14 @@ __device__ __forceinline__ float sgnf(float d) { return d > 0.0f ? 1.0f : (d < 0
 // march, so the maps never leave the chip: memory sees x and y once (their halo
 // again through the caches) and the gradient.
 //
-// The two windows are 154 FMAs per pixel and channel, 63 us on 8 x 1200 x 680 at the
+// The two windows are 154 FMAs per pixel and channel, 50 us on 8 x 1200 x 680 at the
 // rate the vector units reach (2.6 cycles an FMA on a SIMD with vector operands
-// alone, 4.3 with a scalar one: the weights are kept in vector registers), and the
-// halo, the formula and the transposes about as much again.  x, y and the gradient
-// are 235 MB there, 50 us.  It takes 175 us, where two kernels with the maps in
-// memory between them took 348.  One wave for all signals of a strip carries 84
+// alone, 4.4 with a scalar one: the weights are kept in vector registers).  x, y and
+// the gradient are 235 MB there, 50 us.  It takes 175 us, where two kernels with the
+// maps in memory between them took 348.  With the halo, the rows of warm-up, the
+// formula and the transposes a pixel and channel take 320 lane instructions, 98M of a
+// wave: about 130 us of issue at those rates; the LDS is busy 82 us, a quarter of it
+// with bank conflicts, and the waves wait for it and at three barriers a chunk.  One wave for all signals of a strip carries 84
 // sums a lane and leaves two waves to a SIMD, which wait for each other's
 // memory: 174 us without the depth residual, and slower in a call of one view,
 // whose time is that of a chunk.  A wave for each signal carries 24.
@@ -91,8 +93,8 @@ __device__ __forceinline__ float sgnf(float d) { return d > 0.0f ? 1.0f : (d < 0
 //      LDS (lanes = the 64 map columns); along y, four rows at a time, the sums
 //      of the 12 rows in progress kept in registers
 //   B  wave t: SSIM and its derivatives of two of the eight complete map rows
-//   C  wave k < 3: map k along y; transposed (lanes = 8 rows x 8 bands of 7
-//      output columns); along x
+//   C  wave k < 3: map k along y; transposed (lanes = 8 rows x 8 bands of 8
+//      columns, of which 54 are output); along x
 //      then, a wave two rows, the gradient
 //
 // A map row completes three quads of rows after its first input, an output row

@@ -949,8 +949,10 @@ struct VoxelArgs {
 // so the lanes all merge, along chains of one length).
 // LBFGS: a voxel takes two neighbouring lanes, and a wave as few voxels (2 to 32)
 // as 4096 waves can hold them all in: a wave lasts as long as its slowest voxel,
-// and four to a SIMD one after another even that out (100k Gaussians: 2.67 ms
-// with 512 waves, 2.81 with 1024, 2.24 with 2048, 1.81 with 4096, 3.21 with 8192).
+// and four to a SIMD even that out.  The call with 1024 / 2048 / 4096 / 8192 / 16384
+// waves, ms: 5k Gaussians at 5 cm 0.72 / 0.73 / 0.76 / 0.73 / 0.73, 20k 1.51 / 1.18 / 1.22 / 1.04 /
+// 1.20, 100k 3.3 / 2.8 / 2.1 / 3.5 / 4.7, 200k 4.6 / 4.6 / 3.4 / 3.3 / 8.4, 500k 5.5 / 5.5 / 5.5 / 7.0 / 10.1,
+// 2M 33 / 32 / 33 / 33 / 39.
 constexpr int64_t kLbfgsWaves = 4096;
 __device__ __forceinline__ int lbfgs_voxels(int64_t nvox) {
     int v = 2;

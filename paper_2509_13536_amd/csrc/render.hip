@@ -586,10 +586,11 @@ struct SideRankCount {
 // three dependent memory accesses for few pairs, by the compares (two
 // instructions for 64 of them) for many: 13 us for 8.2 thousand pairs and 22 us
 // for 15 thousand, where three byte passes take nine launches of 3-4 us and the
-// time between them.  The line: a 10k-Gaussian view goes from 120 to 101 us by
-// it, 15 thousand visible pairs from 260 to 246 us; the compares grow with the
-// square, the passes hardly, and meet near 20 thousand.  Views are not compared,
-// so it takes one view.
+// time between them.  The whole forward call against that with the passes, us: 200
+// pairs 64 / 84, 5 thousand 77 / 96, 11 thousand 93 / 104, 16384 101 / 107, and in a
+// room of 100k Gaussians (15 thousand) 176 / 176.  The line is where the keys still
+// fit a block's LDS twice on a CU and the two meet.  Views are not compared, so it
+// takes one view.
 constexpr int64_t kRankByCountingMax = 16384;
 constexpr int kRankWaves = 16, kRankParts = 2 * kRankWaves, kRankStep = 16;
 constexpr int kRankPerPart = (int)(kRankByCountingMax / kRankParts);
