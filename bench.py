@@ -26,13 +26,16 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# MI355X: 256 CUs x 4 SIMD x 16 lanes at 2.4 GHz = one non-packed fp32 VALU
-# operation per lane and cycle; HBM3E 8 TB/s.
-PEAK_VALU_GOPS = 256 * 4 * 16 * 2.4  # 39321.6 G lane-ops/s
+# MI355X: 256 CUs x 4 SIMDs x 32 lanes at 2.4 GHz: a wave's fp32 FMA, multiply or
+# add on vector registers (not packed) issues in two cycles (measured: 2.4 with
+# eight waves a SIMD; 4.4 with a scalar operand and for compares, selects and
+# cross-lane operations, 8.4 for a transcendental); HBM3E 8 TB/s.
+PEAK_VALU_GOPS = 256 * 4 * 32 * 2.4  # 78643.2 G lane-ops/s
 PEAK_HBM_GBS = 8000.0
 # Algorithmic VALU lane-operations per blended (pixel, Gaussian) pair - the
 # arithmetic any implementation must do for a Gaussian that contributes to a
-# pixel (a transcendental counts 4, its issue cost).  Forward: 2 offsets,
+# pixel (a transcendental counts 4, its issue cost; a compare 1, though it issues
+# in the time of 2).  Forward: 2 offsets,
 # 3 for the quadratic form, exp (4), times opacity, clamp, 1 - alpha, the
 # transmittance product, 2 threshold tests, alpha T, 4 accumulations = 20.
 # Backward: the forward's 11 to recompute alpha, transmittance recovery
@@ -256,11 +259,11 @@ def configs_bench(only=""):
 # two depths and writes one gradient (12 B).
 LOSS_BYTES_PER_PIXEL = 3 * (8 + 4) + 12
 # Algorithmic VALU lane-operations of the loss per pixel and colour channel (the
-# SSIM stencil dominates; a reciprocal counts 4): first pass 3 products, 5 moments
-# x 11 taps along rows and again along columns (110), SSIM with its three
-# derivatives (about 26 plus 4 reciprocals) = 155; second pass 3 maps x 11 taps
-# x 2 directions (66) and the combination with the L1 term (5) = 71.
-LOSS_OPS_PER_PIXEL_CHANNEL = 155 + 71
+# SSIM stencil dominates; a reciprocal counts 4): x y and (x - y)^2 (3), 4 moments
+# x 11 taps along rows and again along columns (88), SSIM with its three
+# derivatives (25 and 2 reciprocals), 3 maps x 11 taps x 2 directions (66) and the
+# combination with the L1 term (11).
+LOSS_OPS_PER_PIXEL_CHANNEL = 3 + 88 + 33 + 66 + 11
 
 
 def mapping_loss_bench(m, views, out_bufs):
