@@ -136,15 +136,16 @@ __global__ __launch_bounds__(1024) void k_bin_order(const uint32_t *totals, uint
         }
     }
     __syncthreads();
-    uint32_t most = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k)
-        if (i0 + k < n) {
-            atomicAdd(&h[len_class(len[k])], 1u);
-            most = max(most, len[k]);
-        }
-    most = wave_max_u32(most);
-    if (lane_id() == 0) atomicMax(&top, most);
+        if (i0 + k < n) atomicAdd(&h[len_class(len[k])], 1u);
+    if (longest) {  // uniform
+        uint32_t most = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) most = max(most, i0 + k < n ? len[k] : 0u);
+        most = wave_max_u32(most);
+        if (lane_id() == 0) atomicMax(&top, most);
+    }
     __syncthreads();
     if (longest && threadIdx.x == 0) *longest = top;
     // the classes' first slots

@@ -6,7 +6,8 @@
 //   k_pg_count    one thread per keypoint: its pixel (floor(u + 1/2)) and
 //                 patch; integer atomics count the keypoints of each patch
 //                 (exact, so the counts do not depend on the order)
-//   k_pg_depth    one wave per candidate or four (the keypoints, then the s x s lattice
+//   k_pg_depth, k_pg_depth4
+//                 one wave per candidate or four (the keypoints, then the s x s lattice
 //                 of every patch): whether it is kept, and its depth, its own,
 //                 the depth map's or the nearest keypoint's by a brute-force
 //                 scan split over the lanes (fp32 squared distances, ties to the
@@ -130,13 +131,58 @@ __global__ __launch_bounds__(256) void k_pg_resolve(PgArgs a) {
     a.cand_z[c] = z == kNeedSearch ? 0.0f : z;
 }
 
-// A wave takes PER candidates, a lane each for what they have of their own.  Of
-// one still without a depth, the lanes split the keypoints (lane l takes l, l + 64,
-// ..., four in flight), keep their nearest with depth (fp32 squared distance, the
-// first of equal ones), and a lexicographic (distance, index) minimum over the wave
-// gives the nearest, ties to the lower index.  Bound by its chain of loads: 12 us
-// for 5344 candidates and 2000 keypoints, where the search and a launch before it
-// for the rest took 14 + 2.7.
+// The depth of the keypoint nearest to (qx, qy), 0 without one that has a depth.  The
+// lanes split the keypoints (lane l takes l, l + 64, ..., four in flight), keep
+// their nearest with depth (fp32 squared distance, the first of equal ones), and a
+// lexicographic (distance, index) minimum over the wave gives the nearest, ties to
+// the lower index.
+__device__ __forceinline__ float pg_nearest_depth(const PgArgs &a, float qx, float qy) {
+    float best = INFINITY;
+    int arg = (int)a.n_kp;  // none (n_kp < 2^31)
+    constexpr int kAhead = 4;
+    for (int64_t i0 = lane_id(); i0 < a.n_kp; i0 += 64 * kAhead) {
+        float d[kAhead], kx[kAhead], ky[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t i = min(i0 + 64 * u, a.n_kp - 1);  // repeated, the last changes nothing
+            d[u] = a.kp_depth[i];
+            kx[u] = a.kp[2 * i];
+            ky[u] = a.kp[2 * i + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const float dx = qx - kx[u], dy = qy - ky[u];
+            const float d2 = dx * dx + dy * dy;
+            if (d[u] > 0.0f && d2 < best) {
+                best = d2;
+                arg = (int)min(i0 + 64 * u, a.n_kp - 1);
+            }
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const float ob = __shfl_xor(best, off, 64);
+        const int oa = __shfl_xor(arg, off, 64);
+        if (ob < best || (ob == best && oa < arg)) {
+            best = ob;
+            arg = oa;
+        }
+    }
+    return arg < a.n_kp ? a.kp_depth[arg] : 0.0f;
+}
+
+// One wave per candidate.  Bound by its chain of loads: 12 us for 5344 candidates and
+// 2000 keypoints, where the search and a launch before it for the rest took 14 + 2.7.
+__global__ __launch_bounds__(256) void k_pg_depth(PgArgs a) {
+    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (c >= a.n_cand) return;
+    float qx, qy;
+    float z = pg_own_depth(a, c, qx, qy);
+    if (z == kNeedSearch) z = pg_nearest_depth(a, qx, qy);  // wave-uniform
+    if (lane_id() == 0) a.cand_z[c] = z;
+}
+
+// A wave takes four candidates, a lane each for what they have of their own, and
+// searches for those still without a depth in turn.
 // Few candidates take a wave each: what a wave does for one of its own depth then
 // costs less than searches in turn.  From kDepthMany on, where most are samples, a
 // wave takes four: the whole call with a wave for one / four / sixteen, us, 2000
@@ -145,53 +191,19 @@ __global__ __launch_bounds__(256) void k_pg_resolve(PgArgs a) {
 // 172 / 139, 1117 / 1118 / 1130.  Keypoints in the majority search longer: 50k of
 // them, of 52k candidates, 1296 / 1428 / 1729.
 constexpr int64_t kDepthMany = 32768;
-template <int PER>
-__global__ __launch_bounds__(256) void k_pg_depth(PgArgs a) {
+__global__ __launch_bounds__(256) void k_pg_depth4(PgArgs a) {
     const int lane = lane_id();
-    const int64_t c0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * PER;
-    if (c0 >= a.n_cand) return;
-    float ox = 0.0f, oy = 0.0f, z = 0.0f;
-    const int64_t c = PER == 1 ? c0 : c0 + lane;
-    const bool mine = PER == 1 || (lane < PER && c < a.n_cand);
-    if (mine) z = pg_own_depth(a, c, ox, oy);
-    uint64_t left = ballot(mine && z == kNeedSearch);
-    if (PER == 1) left = left ? 1ull : 0ull;  // all lanes hold the one candidate
-    for (; left; left &= left - 1ull) {
+    const int64_t c = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 4 + lane;
+    if (c - lane >= a.n_cand) return;
+    float qx = 0.0f, qy = 0.0f, z = 0.0f;
+    const bool mine = lane < 4 && c < a.n_cand;
+    if (mine) z = pg_own_depth(a, c, qx, qy);
+    for (uint64_t left = ballot(mine && z == kNeedSearch); left; left &= left - 1ull) {
         const int l = __ffsll((long long)left) - 1;
-        const float qx = PER == 1 ? ox : readlane_f(ox, l), qy = PER == 1 ? oy : readlane_f(oy, l);
-        float best = INFINITY;
-        int arg = (int)a.n_kp;  // none (n_kp < 2^31)
-        constexpr int kAhead = 4;
-        for (int64_t i0 = lane; i0 < a.n_kp; i0 += 64 * kAhead) {
-            float d[kAhead], kx[kAhead], ky[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int64_t i = min(i0 + 64 * u, a.n_kp - 1);  // repeated, the last changes nothing
-                d[u] = a.kp_depth[i];
-                kx[u] = a.kp[2 * i];
-                ky[u] = a.kp[2 * i + 1];
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const float dx = qx - kx[u], dy = qy - ky[u];
-                const float d2 = dx * dx + dy * dy;
-                if (d[u] > 0.0f && d2 < best) {
-                    best = d2;
-                    arg = (int)min(i0 + 64 * u, a.n_kp - 1);
-                }
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            const float ob = __shfl_xor(best, off, 64);
-            const int oa = __shfl_xor(arg, off, 64);
-            if (ob < best || (ob == best && oa < arg)) {
-                best = ob;
-                arg = oa;
-            }
-        }
-        if (PER == 1 || lane == l) z = arg < a.n_kp ? a.kp_depth[arg] : 0.0f;
+        const float found = pg_nearest_depth(a, readlane_f(qx, l), readlane_f(qy, l));
+        if (lane == l) z = found;
     }
-    if (PER == 1 ? lane == 0 : mine) a.cand_z[c] = z;
+    if (mine) a.cand_z[c] = z;
 }
 
 struct LoadKept {
@@ -322,9 +334,9 @@ extern "C" mgs_status mgs_patch_grid_sample(const mgs_camera *cam, const float *
         if (n_kp > 0) k_pg_count<<<(unsigned)ceil_div(n_kp, 256), 256, 0, s>>>(a);
     }
     if (n_kp > 0 && a.n_cand >= kDepthMany && a.n_cand >= 4 * n_kp)
-        k_pg_depth<4><<<(unsigned)ceil_div(a.n_cand, 16), 256, 0, s>>>(a);
+        k_pg_depth4<<<(unsigned)ceil_div(a.n_cand, 16), 256, 0, s>>>(a);
     else if (n_kp > 0)
-        k_pg_depth<1><<<(unsigned)ceil_div(a.n_cand, 4), 256, 0, s>>>(a);
+        k_pg_depth<<<(unsigned)ceil_div(a.n_cand, 4), 256, 0, s>>>(a);
     else k_pg_resolve<<<(unsigned)ceil_div(a.n_cand, 256), 256, 0, s>>>(a);
     MGS_LAUNCHED();
     PgWrite w;
