@@ -265,7 +265,7 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
             if (out_own) {
                 const float o0 = map[0][row_at(r) + lane], o1 = map[1][row_at(r) + lane], o2 = map[2][row_at(r) + lane];
                 const float d = xo[u] - yo[u];
-                const float gs = o0 + (2.0f * xo[u] * o1 + yo[u] * o2);  // no FMA: 0 of equal images
+                const float gs = o0 + (xo[u] * o1 + yo[u] * o2);  // no FMA: 0 of equal images
                 a.d_rgb[cbase + (int64_t)oy * W + ox] = __builtin_fmaf(-ks, gs, kl1 * sgnf(d));
                 sL += fabsf(d);
             }
@@ -320,16 +320,16 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
                 const bool in = col_in && gy >= 0 && gy < H;
                 const float mx = mx2[u], my = my2[u], e = e2[u], p = p2[u];
                 // SSIM = (1 - a) (1 - b), a and b differences of the two images over sums,
-                // so that equal windows give 1, no first derivative, and the second and
-                // third to a factor of -2, exactly; 1 - SSIM keeps its small values
+                // so that equal windows give 1, no derivative by E[x], and those by E[x^2]
+                // (twice it) and E[xy] opposite, exactly; 1 - SSIM keeps its small values
                 const float dm = mx - my, dd = dm * dm, ed = e - dd;
                 const float iC = __builtin_amdgcn_rcpf(__builtin_fmaf(mx, mx, my * my) + kC1);
                 const float iD = __builtin_amdgcn_rcpf(__builtin_fmaf(2.0f, __builtin_fmaf(-mx, my, p), ed) + kC2);
-                const float a1 = dd * iC, b1 = ed * iD, u1 = 1.0f - a1, v1 = 1.0f - b1, uD = u1 * iD;
-                const float d0 = 2.0f * __builtin_fmaf(v1 * iC, __builtin_fmaf(-mx, u1, my), uD * __builtin_fmaf(mx, v1, -my));
+                const float a1 = dd * iC, b1 = ed * iD, u1 = 1.0f - a1, v1 = 1.0f - b1, uD = 2.0f * u1 * iD;
+                const float d0 = __builtin_fmaf(2.0f * v1 * iC, __builtin_fmaf(-mx, u1, my), uD * __builtin_fmaf(mx, v1, -my));
                 M[0][u] = in ? d0 : 0.0f;
                 M[1][u] = in ? -uD * v1 : 0.0f;
-                M[2][u] = in ? 2.0f * uD : 0.0f;
+                M[2][u] = in ? uD : 0.0f;
                 if (gy >= r0 && gy < rend) sS += col_own ? __builtin_fmaf(-a1, b1, a1 + b1) : 0.0f;
             }
 #pragma unroll
