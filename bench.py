@@ -261,9 +261,9 @@ LOSS_BYTES_PER_PIXEL = 3 * (8 + 4) + 12
 # Algorithmic VALU lane-operations of the loss per pixel and colour channel (the
 # SSIM stencil dominates; a reciprocal counts 4): x y and (x - y)^2 (3), 4 moments
 # x 11 taps along rows and again along columns (88), SSIM with its three
-# derivatives (25 and 2 reciprocals), 3 maps x 11 taps x 2 directions (66) and the
+# derivatives (23 and 2 reciprocals), 3 maps x 11 taps x 2 directions (66) and the
 # combination with the L1 term (10).
-LOSS_OPS_PER_PIXEL_CHANNEL = 3 + 88 + 33 + 66 + 10
+LOSS_OPS_PER_PIXEL_CHANNEL = 3 + 88 + 31 + 66 + 10
 
 
 def mapping_loss_bench(m, views, out_bufs):

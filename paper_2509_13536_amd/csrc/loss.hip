@@ -81,7 +81,7 @@ __device__ __forceinline__ float sgnf(float d) { return d > 0.0f ? 1.0f : (d < 0
 // alone, 4.4 with a scalar one: the weights are kept in vector registers).  x, y and
 // the gradient are 235 MB there, 50 us.  It takes 175 us, where two kernels with the
 // maps in memory between them took 348.  With the halo, the rows of warm-up, the
-// formula and the transposes a pixel and channel take 320 lane instructions, 98M of a
+// formula and the transposes a pixel and channel take 316 lane instructions, 97M of a
 // wave: about 130 us of issue at those rates; the LDS is busy 82 us, a quarter of it
 // with bank conflicts, and the waves wait for it and at three barriers a chunk.  One wave for all signals of a strip carries 84
 // sums a lane and leaves two waves to a SIMD, which wait for each other's
@@ -211,7 +211,7 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
     const bool out_own = lane < kSC && ox < W;
     const int at_col = 12 * lane;                     // its place in the column layout
     const int at_band = row_at(row) + 8 * band;       // this lane's band of 8 in the row layout
-    const float kl1 = (1.0f - a.lam) * inv_n3, ks = a.lam * inv_n3;
+    const float kl1 = (1.0f - a.lam) * inv_n3, ks = 2.0f * (a.lam * inv_n3);  // the maps are halves
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     f4 g1[3] = {zero, zero, zero}, g2[3] = {zero, zero, zero};
     // the weights in vector registers: an FMA with a scalar operand issues at
@@ -321,12 +321,13 @@ __device__ __forceinline__ void ssim_tile(const SsimArgs &a, int64_t item) {
                 const float mx = mx2[u], my = my2[u], e = e2[u], p = p2[u];
                 // SSIM = (1 - a) (1 - b), a and b differences of the two images over sums,
                 // so that equal windows give 1, no derivative by E[x], and those by E[x^2]
-                // (twice it) and E[xy] opposite, exactly; 1 - SSIM keeps its small values
+                // (twice it) and E[xy] opposite, exactly; 1 - SSIM keeps its small values.
+                // The maps hold half of each
                 const float dm = mx - my, dd = dm * dm, ed = e - dd;
                 const float iC = __builtin_amdgcn_rcpf(__builtin_fmaf(mx, mx, my * my) + kC1);
                 const float iD = __builtin_amdgcn_rcpf(__builtin_fmaf(2.0f, __builtin_fmaf(-mx, my, p), ed) + kC2);
-                const float a1 = dd * iC, b1 = ed * iD, u1 = 1.0f - a1, v1 = 1.0f - b1, uD = 2.0f * u1 * iD;
-                const float d0 = __builtin_fmaf(2.0f * v1 * iC, __builtin_fmaf(-mx, u1, my), uD * __builtin_fmaf(mx, v1, -my));
+                const float a1 = dd * iC, b1 = ed * iD, u1 = 1.0f - a1, v1 = 1.0f - b1, uD = u1 * iD;
+                const float d0 = __builtin_fmaf(v1 * iC, __builtin_fmaf(-mx, u1, my), uD * __builtin_fmaf(mx, v1, -my));
                 M[0][u] = in ? d0 : 0.0f;
                 M[1][u] = in ? -uD * v1 : 0.0f;
                 M[2][u] = in ? uD : 0.0f;
